@@ -393,7 +393,7 @@ def _stream(case, h, tags):
             o = 0 if i == 0 else i + H if i <= H else i - H
             src = torch.roll(tags, **back)
             out[i] = torch.where(src == TAG[case["model"]], out[i], h[o])
-            out[i] += torch.where(src >= lbm.TAG_WALL0, 6.0 * w[i] * sum(c[i][a] * LID[a] for a in range(3)), 0.0)
+            out[i] += (src >= lbm.TAG_WALL0).double() * (6.0 * w[i] * sum(c[i][a] * LID[a] for a in range(3)))
     if case["geom"] != "periodic":
         out[:, tags != TAG[case["model"]]] = 0.0
     return out
