@@ -123,6 +123,24 @@ enum GatherMode : int { G_POPS = 0, G_FIELDS = 1, G_CELLS = 2 };
 
 template <int Q, int P>
 hipError_t launch_step(const StepParams &p, int ms, bool tagged, int mode, int parity, hipStream_t s);
+// The two-step kernel (lbm_two.h): blocks of tx x ty nodes that march over
+// `chunk` planes.
+struct TwoTiles {
+    int tx, ty, tiles_x, tiles_y, chunk;
+    int n_blocks, per_xcd;    // blocks in all, and ceil(n_blocks / 8)
+};
+// Nodes of a tile with its halo, at most, by precision: 130 x 6 (two blocks' LDS
+// would not fit a CU in any case), in FP64 66 x 6 (LDS, and 256 registers a lane).
+constexpr int two_region(int prec) { return prec == LBM_F64 ? 396 : 780; }
+constexpr int two_max_tx(int prec) { return prec == LBM_F64 ? 64 : 128; }
+// Model sets it is built for.
+constexpr bool two_models(int ms) {
+    return ms == MS_BGK || ms == MS_TRT || ms == MS_REG || ms == MS_RR || ms == (MS_BGK | MS_SMAG);
+}
+// Two steps of the whole lattice from p.pops into dst, layout parity unchanged.
+template <int Q, int P>
+hipError_t launch_two_steps(const StepParams &p, void *dst, const TwoTiles &w, int ms, bool tagged, int parity,
+                            hipStream_t s);
 template <int Q>
 // sector_log2: log2 of the nodes per 64-byte storage sector in the lattice's
 // precision; odd_fill: also mark the odd-step filler targets.

@@ -375,17 +375,184 @@ __device__ __forceinline__ void collide_closure(const C (&h)[Q], int tag, bool l
     });
 }
 
-// MOM: regularized / recursive-regularized lattices take the moment-only
-// update (collide_regularized); the caller decides where that pays.
-template <int Q, typename C, int MS, bool MOM = false>
+// BGK and BGK + Smagorinsky, population by population: with cu = c.u,
+//   t = drho - 3/2 rho u.u + 9/2 rho cu^2,  feq_k = w (t + 3 rho cu),  feq_k' = w (t - 3 rho cu)
+//   h* = h - omega (h - feq)  (+ Guo terms, skipped as a block without a body force)
+// The Smagorinsky rate takes the momentum flux from the second moment of h less
+// the equilibrium's (see collide_closure).  Every product-sum is an explicit
+// fused multiply-add, so the rounding does not depend on the kernel around it.
+template <int Q, typename C, int MS>
+__device__ __forceinline__ void collide_bgk(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q]) {
+    constexpr int H = (Q - 1) / 2;
+    constexpr bool SMAG = (MS & MS_SMAG) != 0;
+    auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
+    C drho = h[0], jx = C(0), jy = C(0), jz = C(0);
+    C sxx = C(0), syy = C(0), szz = C(0), sxy = C(0), sxz = C(0), syz = C(0);
+    sfor<H>([&](auto K) {
+        constexpr int k = decltype(K)::value + 1;
+        using Vk = V<Q, k>;
+        const C e = h[k] + h[k + H], o = h[k] - h[k + H];
+        drho += e;
+        if constexpr (Vk::x != 0) jx += C(Vk::x) * o;
+        if constexpr (Vk::y != 0) jy += C(Vk::y) * o;
+        if constexpr (Vk::z != 0) jz += C(Vk::z) * o;
+        if constexpr (SMAG) {
+            if constexpr (Vk::x != 0) sxx += e;
+            if constexpr (Vk::y != 0) syy += e;
+            if constexpr (Vk::z != 0) szz += e;
+            if constexpr (Vk::x * Vk::y != 0) sxy += C(Vk::x * Vk::y) * e;
+            if constexpr (Vk::x * Vk::z != 0) sxz += C(Vk::x * Vk::z) * e;
+            if constexpr (Vk::y * Vk::z != 0) syz += C(Vk::y * Vk::z) * e;
+        }
+    });
+    const C rho = (C)p.rho0 + drho;
+    const C inv_rho = C(1) / rho;
+    const C ux = fm(C(0.5), (C)p.force[0], jx) * inv_rho;
+    const C uy = fm(C(0.5), (C)p.force[1], jy) * inv_rho;
+    const C uz = fm(C(0.5), (C)p.force[2], jz) * inv_rho;
+    C w = (C)p.omega;
+    if constexpr (SMAG) {
+        const C d3 = drho * C(1.0 / 3.0);
+        const C rx = rho * ux, ry = rho * uy, rz = rho * uz;
+        const C pxx = fm(-rx, ux, sxx - d3), pyy = fm(-ry, uy, syy - d3), pzz = fm(-rz, uz, szz - d3);
+        const C pxy = fm(-rx, uy, sxy), pxz = fm(-rx, uz, sxz), pyz = fm(-ry, uz, syz);
+        const C q2 = fm(pxx, pxx, fm(pyy, pyy, pzz * pzz)), qo = fm(pxy, pxy, fm(pxz, pxz, pyz * pyz));
+        const C qn = sqrt(fm(C(2), qo, q2));
+        const C tau0 = (C)p.tau;
+        const C tau_eff = C(0.5) * (tau0 + sqrt(fm((C)p.smag_c * qn, inv_rho, tau0 * tau0)));
+        if (tag == LBM_TAG_BGK_SMAG) w = C(1) / tau_eff;
+    }
+    const C r3 = C(3) * rho, r45 = C(4.5) * rho;
+    const C base = fm(C(-1.5) * rho, fm(ux, ux, fm(uy, uy, uz * uz)), drho);
+    hs[0] = fm(-w, fm(C(-V<Q, 0>::w), base, h[0]), h[0]);
+    sfor<H>([&](auto K) {
+        constexpr int k = decltype(K)::value + 1;
+        using Vk = V<Q, k>;
+        C cu = C(0);
+        if constexpr (Vk::x != 0) cu += C(Vk::x) * ux;
+        if constexpr (Vk::y != 0) cu += C(Vk::y) * uy;
+        if constexpr (Vk::z != 0) cu += C(Vk::z) * uz;
+        const C t = fm(r45 * cu, cu, base);
+        const C a = fm(r3, cu, t), b = fm(-r3, cu, t);
+        hs[k] = fm(-w, fm(C(-Vk::w), a, h[k]), h[k]);
+        hs[k + H] = fm(-w, fm(C(-Vk::w), b, h[k + H]), h[k + H]);
+    });
+    if (p.has_force) {  // uniform
+        asm volatile("");  // keeps the compiler from computing the block without the branch
+        const C Fx = (C)p.force[0], Fy = (C)p.force[1], Fz = (C)p.force[2];
+        const C uF = fm(ux, Fx, fm(uy, Fy, uz * Fz));
+        const C g = fm(C(-0.5), w, C(1));
+        hs[0] = fm(C(-3.0 * V<Q, 0>::w) * g, uF, hs[0]);
+        sfor<H>([&](auto K) {
+            constexpr int k = decltype(K)::value + 1;
+            using Vk = V<Q, k>;
+            C cu = C(0), cF = C(0);
+            if constexpr (Vk::x != 0) cu += C(Vk::x) * ux, cF += C(Vk::x) * Fx;
+            if constexpr (Vk::y != 0) cu += C(Vk::y) * uy, cF += C(Vk::y) * Fy;
+            if constexpr (Vk::z != 0) cu += C(Vk::z) * uz, cF += C(Vk::z) * Fz;
+            const C gw = C(3.0 * Vk::w) * g;
+            const C even = fm(C(3) * cu, cF, -uF);
+            hs[k] = fm(gw, even + cF, hs[k]);
+            hs[k + H] = fm(gw, even - cF, hs[k + H]);
+        });
+    }
+}
+
+// Two-relaxation-time update for lattices whose fluid nodes all use it, pair by
+// pair: h* = h - omega+ (even part of h - heq) -+ omega- (odd part), plus the Guo
+// terms.  Every product-sum is an explicit fused multiply-add,
+// so the rounding does not depend on the kernel around it.
+// FORCE: the Guo terms are compiled in.  Without a body force they are exactly
+// zero, so both forms give the same result.
+template <int Q, typename C, bool FORCE>
+__device__ __forceinline__ void collide_trt(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q]) {
+    constexpr int H = (Q - 1) / 2;
+    auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
+    C drho = C(0), px = C(0), py = C(0), pz = C(0);
+    sfor<Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        using Vi = V<Q, i>;
+        drho += h[i];
+        if constexpr (Vi::x == 1) px += h[i];
+        if constexpr (Vi::x == -1) px -= h[i];
+        if constexpr (Vi::y == 1) py += h[i];
+        if constexpr (Vi::y == -1) py -= h[i];
+        if constexpr (Vi::z == 1) pz += h[i];
+        if constexpr (Vi::z == -1) pz -= h[i];
+    });
+    const C Fx = (C)p.force[0], Fy = (C)p.force[1], Fz = (C)p.force[2];
+    const C rho = (C)p.rho0 + drho;
+    const C inv_rho = C(1) / rho;
+    px = fm(C(0.5), Fx, px);
+    py = fm(C(0.5), Fy, py);
+    pz = fm(C(0.5), Fz, pz);
+    const C ux = px * inv_rho, uy = py * inv_rho, uz = pz * inv_rho;
+    const C uu = fm(uz, uz, fm(ux, ux, uy * uy));
+    const C wp = (C)p.omega, wm = tag == LBM_TAG_TRT ? (C)p.omega_minus : (C)p.omega;
+    const C uu15 = C(-1.5) * uu;
+    hs[0] = fm(-fm(C(-V<Q, 0>::w), fm(C(-1.5) * rho, uu, drho), h[0]), wp, h[0]);
+    // c.u of pair k
+    auto cu_of = [&](auto K) {
+        using Vk = V<Q, decltype(K)::value>;
+        C cu = C(0);
+        if constexpr (Vk::x != 0) cu = C(Vk::x) * ux;
+        if constexpr (Vk::y != 0) cu = Vk::x == 0 ? C(Vk::y) * uy : fm(C(Vk::y) * py, inv_rho, cu);
+        if constexpr (Vk::z != 0) cu = Vk::x == 0 && Vk::y == 0 ? C(Vk::z) * uz : fm(C(Vk::z) * pz, inv_rho, cu);
+        return cu;
+    };
+    auto pairs = [&](auto force_c) {
+        constexpr bool kForce = decltype(force_c)::value;
+        C gp = C(0), gm = C(0), uF3 = C(0);
+        if constexpr (kForce) {
+            gp = fm(wp, C(-0.5), C(1));
+            gm = fm(wm, C(-0.5), C(1));
+            const C uF = fm(uz, Fz, fm(ux, Fx, uy * Fy));
+            uF3 = C(-3) * uF;
+            hs[0] = fm(gp, C(-3.0 * V<Q, 0>::w) * uF, hs[0]);
+        }
+        sfor<H>([&](auto K) {
+#pragma clang fp contract(off)  // A and B are rounded before they are added
+            constexpr int k = decltype(K)::value + 1;
+            using Vk = V<Q, k>;
+            const C cu = cu_of(std::integral_constant<int, k>{});
+            const C ev = C(Vk::w) * fm(rho, fm(cu, C(4.5) * cu, uu15), drho);
+            const C od = (C(3.0 * Vk::w) * rho) * cu;
+            C A = -(fm(h[k] + h[k + H], C(0.5), -ev) * wp);
+            C B = -(fm(h[k] - h[k + H], C(0.5), -od) * wm);
+            if constexpr (kForce) {
+                C cF = C(0);
+                if constexpr (Vk::x != 0) cF += C(Vk::x) * Fx;
+                if constexpr (Vk::y != 0) cF += C(Vk::y) * Fy;
+                if constexpr (Vk::z != 0) cF += C(Vk::z) * Fz;
+                A = fm(gp, C(Vk::w) * fm(cF, C(9) * cu, uF3), A);
+                B = fm(C(3.0 * Vk::w) * cF, gm, B);
+            }
+            hs[k] = (h[k] + A) + B;
+            hs[k + H] = (h[k + H] + A) - B;
+        });
+    };
+    pairs(std::integral_constant<bool, FORCE>{});
+}
+
+// Regularized / recursive-regularized lattices take the moment-only update
+// (collide_regularized).
+template <int Q, typename C, int MS, bool FORCE = true>
 __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live, const StepParams &p, C (&hs)[Q]) {
     if constexpr (MS == MS_STREAM) {
         // collision switched off: the step only streams (and bounces back)
         sfor<Q>([&](auto I) { hs[decltype(I)::value] = h[decltype(I)::value]; });
         return;
     }
-    if constexpr (MOM && (MS == MS_REG || MS == MS_RR)) {
+    if constexpr (MS == MS_REG || MS == MS_RR) {
         collide_regularized<Q, C, MS>(h, tag, p, hs);
+        return;
+    }
+    if constexpr (MS == MS_BGK || MS == (MS_BGK | MS_SMAG)) {
+        collide_bgk<Q, C, MS>(h, tag, p, hs);
+        return;
+    }
+    if constexpr (MS == MS_TRT) {
+        collide_trt<Q, C, FORCE>(h, tag, p, hs);
         return;
     }
     if constexpr (MS == (MS_BGK | MS_SMAG | MS_MLP)) {
@@ -801,10 +968,7 @@ __global__ __launch_bounds__(256) void k_collide_stream(StepParams p) {
 
         if constexpr (MODE != MODE_REDUCE) {
             C hs[Q];
-            // moment-only regularized update in FP16 storage and FP64 (fewer
-            // registers: FP16 +10-14%, FP64 RR +4%); FP32 measured 0.5-2%
-            // slower with it and keeps the general update
-            collide_node<Q, C, MS, P != 1>(h, tag, live, p, hs);
+            collide_node<Q, C, MS>(h, tag, live, p, hs);
 
             // moving-wall term where x + c_i is a moving wall (nodes next to one only)
             if constexpr (TAGGED && WALLS) {
@@ -976,7 +1140,7 @@ __global__ __launch_bounds__(256) void k_collide_pair_even(StepParams p) {
             constexpr int i = decltype(I)::value;
             h[i] = k == 0 ? half_lo(u[i]) : half_hi(u[i]);
         });
-        collide_node<Q, C, MS, true>(h, tag, true, p, hs);
+        collide_node<Q, C, MS>(h, tag, true, p, hs);
         sfor<Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (k == 0) o[i] = half_bits(hs[i]);
@@ -1184,14 +1348,19 @@ __global__ __launch_bounds__(256) void k_face(AuxParams a, int face, int unpack,
 // and the odd step lose with any cap.
 constexpr unsigned kEvenLdsCap = 41u << 10;
 
+// The same for both parities of FP32 brick-layout lattices, at four workgroups a
+// CU: 256^3 porous D3Q19 TRT 190.5 us a step against 197 without a cap.
+constexpr unsigned kBrickLdsCap = 40000u;
+
 template <int Q, int P, int MS, bool TG, int MODE, int ADDR>
 static hipError_t launch_step_rows(const StepParams &p, int parity, hipStream_t s) {
     const dim3 grid(8 * p.tiles_per_xcd), block(256);
-    constexpr unsigned lds_even = (ADDR == 1 && TG && P != 2) ? kEvenLdsCap : 0u;
+    constexpr unsigned lds_brick = (ADDR == 2 && P == 1) ? kBrickLdsCap : 0u;
+    constexpr unsigned lds_even = (ADDR == 1 && TG && P != 2) ? kEvenLdsCap : lds_brick;
     if (parity == 0)
         k_collide_stream<Q, P, MS, TG, MODE, 0, ADDR><<<grid, block, lds_even, s>>>(p);
     else
-        k_collide_stream<Q, P, MS, TG, MODE, 1, ADDR><<<grid, block, 0, s>>>(p);
+        k_collide_stream<Q, P, MS, TG, MODE, 1, ADDR><<<grid, block, lds_brick, s>>>(p);
     return hipGetLastError();
 }
 
