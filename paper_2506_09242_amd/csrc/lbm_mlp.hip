@@ -298,95 +298,138 @@ extern "C" lbm_status lbm_filter_snapshot(lbm_lattice *fine, int factor, float *
 
 // ------------------------------------------------------------ training
 namespace lbmd {
-constexpr int ACT = 136;  // per-sample record: xhat 7 | h1 32 | h2 32 | d1 32 | d2 32 | d3 1
-constexpr int A_X = 0, A_H1 = 7, A_H2 = 39, A_D1 = 71, A_D2 = 103, A_D3 = 135;
+constexpr int kTrainSamples = 128;  // samples a block works on at a time, 32 a wave
+constexpr int kTrainPitch = 33;     // LDS row of one sample (32 neurons and a pad: no bank conflicts)
 
-// Forward and backward of one sample per thread (FP32); loss = scale * (y - t)^2.
-__global__ __launch_bounds__(256) void k_fwd_bwd(const float *P, const float *feat, const float *target,
-                                                 const long long *idx, long long base, int nb, long long n,
-                                                 float scale, float *act, float *loss) {
-    __shared__ float sp[NP];
-    for (int k = threadIdx.x; k < NP; k += 256) sp[k] = P[k];
+// Forward and backward of 128 samples per block and pass on FP32 matrix cores
+// (v_mfma_f32_32x32x2f32: FP32 operands, products and sums), and the block's sum
+// of the gradient in part[block][NP + 1] (packed parameter order, then the loss).
+// Bound by latency: the 4096 samples of a mini-batch are 31 MFLOP, 32 blocks; one
+// thread per sample with its record in memory and one thread per parameter and 256
+// samples took 21 + 123 us a batch, this 13 (with the parameters staged through
+// LDS first, and the next indices loaded ahead, 13.7).
+//
+// Layouts: neurons are the M dimension, samples the N dimension, so accumulator
+// register r of lane l holds neuron nr(r) = 8 (r / 4) + 4 (l / 32) + r % 4 of
+// sample l % 32.  The next product takes register r as its B operand as it is
+// (lane half g the K slot of neuron nr(r)), with the weights' columns in the same
+// order.  The gradient products sum over samples, so their operands go through
+// LDS: wave 0 forms dW2 = d2 h1^T, waves 1, 2 and 3 the products of d1, d2 and h2
+// with X = [x, 1, d3] (dW1 and db1, db2, dW3).
+__global__ __launch_bounds__(256) void k_train(const float *P, const float *feat, const float *target,
+                                               const long long *idx, long long base, int nb, long long n, float scale,
+                                               float *part) {
+    __shared__ float sh[4][kTrainSamples * kTrainPitch];  // d2, d1, h2, h1
+    __shared__ float sx[kTrainSamples * 9];
+    __shared__ float s_sum[4][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane >> 5, c = lane & 31;
+    auto nr = [&](int r) { return 8 * (r / 4) + 4 * g + (r % 4); };
+
+    float w1[4], w2[16], w2t[16], w3[16], mean[4], sd[4];
+    f32x16 b1, b2;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = 2 * j + g;
+        w1[j] = k < 7 ? P[OW1 + c * 7 + k] : 0.0f;
+        mean[j] = k < 7 ? P[OMEAN + k] : 0.0f;
+        sd[j] = k < 7 ? P[OSTD + k] : 1.0f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        w2[r] = P[OW2 + c * 32 + nr(r)];
+        w2t[r] = P[OW2 + nr(r) * 32 + c];
+        w3[r] = P[OW3 + nr(r)];
+        b1[r] = P[OB1 + nr(r)];
+        b2[r] = P[OB2 + nr(r)];
+    }
+    const float b3 = P[OB3];
+    const f32x16 zero = {};
+    f32x16 acc = zero;
+    float lsum = 0.0f, dsum = 0.0f;
+    for (int b0 = blockIdx.x * kTrainSamples; b0 < nb; b0 += gridDim.x * kTrainSamples) {
+        const int sl = wave * 32 + c;  // the lane's sample in the block
+        const int b = b0 + sl;
+        long long s = b < nb ? (idx ? idx[base + b] : base + b) : -1;
+        const bool use = s >= 0 && s < n;  // an out-of-range sample contributes nothing
+        if (!use) s = 0;
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 2 * j + g;
+            x[j] = use && k < 7 ? (feat[s * 7 + k] - mean[j]) / sd[j] : 0.0f;
+        }
+        const float t = use ? target[s] : 0.0f;
+        f32x16 z1 = b1, z2 = b2, d1 = zero;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z1 = __builtin_amdgcn_mfma_f32_32x32x2f32(w1[j], x[j], z1, 0, 0, 0);
+        float h1[16], h2[16], d2[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) h1[r] = z1[r] > 0.0f ? z1[r] : 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z2 = __builtin_amdgcn_mfma_f32_32x32x2f32(w2[r], h1[r], z2, 0, 0, 0);
+        float z3 = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            h2[r] = z2[r] > 0.0f ? z2[r] : 0.0f;
+            z3 += w3[r] * h2[r];
+        }
+        z3 += __shfl_xor(z3, 32, 64);
+        z3 += b3;
+        const float res = softplus_f(z3) - t;
+        const float sig = 1.0f / (1.0f + expf(-z3));
+        const float d3 = use ? scale * 2.0f * res * sig : 0.0f;
+        if (g == 0) {
+            lsum += use ? scale * res * res : 0.0f;
+            dsum += d3;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            d2[r] = z2[r] > 0.0f ? d3 * w3[r] : 0.0f;
+            d1 = __builtin_amdgcn_mfma_f32_32x32x2f32(w2t[r], d2[r], d1, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int a = sl * kTrainPitch + nr(r);
+            sh[0][a] = d2[r];
+            sh[1][a] = z1[r] > 0.0f ? d1[r] : 0.0f;
+            sh[2][a] = h2[r];
+            sh[3][a] = h1[r];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sx[sl * 9 + 2 * j + g] = 2 * j + g < 7 ? x[j] : 1.0f;
+        if (g == 0) sx[sl * 9 + 8] = d3;
+        __syncthreads();
+        const float *sa = sh[wave == 0 || wave == 2 ? 0 : (wave == 1 ? 1 : 2)];
+#pragma unroll 8
+        for (int j = 0; j < kTrainSamples / 2; ++j) {
+            const int q = 2 * j + g;
+            const float bv = wave == 0 ? sh[3][q * kTrainPitch + c] : (c < 9 ? sx[q * 9 + c] : 0.0f);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sa[q * kTrainPitch + c], bv, acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // acc[r]: row nr(r) (neuron), column c
+    float *out = part + (long long)blockIdx.x * (NP + 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int o = nr(r);
+        if (wave == 0) out[OW2 + o * 32 + c] = acc[r];
+        else if (wave == 1 && c < 8) out[c < 7 ? OW1 + o * 7 + c : OB1 + o] = acc[r];
+        else if (wave == 2 && c == 7) out[OB2 + o] = acc[r];
+        else if (wave == 3 && c == 8) out[OW3 + o] = acc[r];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lsum += __shfl_xor(lsum, o, 64);
+        dsum += __shfl_xor(dsum, o, 64);
+    }
+    if (lane == 0) s_sum[wave][0] = lsum, s_sum[wave][1] = dsum;
     __syncthreads();
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= nb) return;
-    long long s = idx ? idx[base + b] : base + b;
-    float *r = act + (long long)b * ACT;
-    if (s < 0 || s >= n) {  // out-of-range sample index: contributes nothing
-        for (int k = 0; k < ACT; ++k) r[k] = 0.0f;
-        loss[b] = 0.0f;
-        return;
+    if (threadIdx.x < 14) out[OMEAN + threadIdx.x] = 0.0f;  // mean and std are not trained
+    if (threadIdx.x == 0) {
+        out[NP] = (s_sum[0][0] + s_sum[1][0]) + (s_sum[2][0] + s_sum[3][0]);
+        out[OB3] = (s_sum[0][1] + s_sum[1][1]) + (s_sum[2][1] + s_sum[3][1]);
     }
-    float x[7];
-    for (int k = 0; k < 7; ++k) {
-        x[k] = (feat[s * 7 + k] - sp[OMEAN + k]) / sp[OSTD + k];
-        r[A_X + k] = x[k];
-    }
-    float z1[32], h1[32], z2[32], h2[32];
-    for (int o = 0; o < 32; ++o) {
-        float a = sp[OB1 + o];
-        for (int k = 0; k < 7; ++k) a += sp[OW1 + o * 7 + k] * x[k];
-        z1[o] = a;
-        h1[o] = a > 0.0f ? a : 0.0f;
-        r[A_H1 + o] = h1[o];
-    }
-    for (int o = 0; o < 32; ++o) {
-        float a = sp[OB2 + o];
-        for (int k = 0; k < 32; ++k) a += sp[OW2 + o * 32 + k] * h1[k];
-        z2[o] = a;
-        h2[o] = a > 0.0f ? a : 0.0f;
-        r[A_H2 + o] = h2[o];
-    }
-    float z3 = sp[OB3];
-    for (int k = 0; k < 32; ++k) z3 += sp[OW3 + k] * h2[k];
-    const float y = softplus_f(z3);
-    const float res = y - target[s];
-    loss[b] = scale * res * res;
-    const float sig = 1.0f / (1.0f + expf(-z3));
-    const float d3 = scale * 2.0f * res * sig;
-    r[A_D3] = d3;
-    float d2[32];
-    for (int o = 0; o < 32; ++o) {
-        d2[o] = z2[o] > 0.0f ? d3 * sp[OW3 + o] : 0.0f;
-        r[A_D2 + o] = d2[o];
-    }
-    for (int k = 0; k < 32; ++k) {
-        float a = 0.0f;
-        for (int o = 0; o < 32; ++o) a += sp[OW2 + o * 32 + k] * d2[o];
-        r[A_D1 + k] = z1[k] > 0.0f ? a : 0.0f;
-    }
-}
-
-// Partial gradients of `chunk` consecutive samples; part[c][k], k < NP, and
-// part[c][NP] = partial loss.  Fixed summation order.
-__global__ __launch_bounds__(256) void k_grad_partial(const float *act, const float *loss, int nb, int chunk,
-                                                      float *part) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    const int c = blockIdx.y;
-    if (k > NP) return;
-    const int b0 = c * chunk, b1 = min(nb, b0 + chunk);
-    float g = 0.0f;
-    if (k == NP) {
-        for (int b = b0; b < b1; ++b) g += loss[b];
-    } else if (k < OB1) {
-        const int o = k / 7, i = k % 7;
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D1 + o] * act[(long long)b * ACT + A_X + i];
-    } else if (k < OW2) {
-        const int o = k - OB1;
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D1 + o];
-    } else if (k < OB2) {
-        const int o = (k - OW2) / 32, i = (k - OW2) % 32;
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D2 + o] * act[(long long)b * ACT + A_H1 + i];
-    } else if (k < OW3) {
-        const int o = k - OB2;
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D2 + o];
-    } else if (k < OB3) {
-        const int i = k - OW3;
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D3] * act[(long long)b * ACT + A_H2 + i];
-    } else if (k == OB3) {
-        for (int b = b0; b < b1; ++b) g += act[(long long)b * ACT + A_D3];
-    }
-    part[(long long)c * (NP + 1) + k] = g;
 }
 
 // Plain zero fill (used instead of memset so callers may capture the work).
@@ -395,22 +438,38 @@ __global__ __launch_bounds__(256) void k_zero(float *p, long long n) {
     if (t < n) p[t] = 0.0f;
 }
 
-// Sum chunk partials in order: out[k] = sum_c part[c][k], k <= NP.
-__global__ __launch_bounds__(256) void k_grad_sum(const float *part, int nchunks, float *out) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k > NP) return;
+// Sum of the block partials of parameter k = 64 blockIdx.x + thread % 64: four
+// runs of rows, each in order, then the runs in order.  Valid in threads 0..63.
+__device__ __forceinline__ float row_sum(const float *part, int rows, int k) {
+    __shared__ float s[4][64];
+    const int run = threadIdx.x >> 6, per = (rows + 3) / 4;
+    const int r0 = run * per, r1 = min(rows, r0 + per);
     float g = 0.0f;
-    for (int c = 0; c < nchunks; ++c) g += part[(long long)c * (NP + 1) + k];
-    out[k] = g;
+    if (k <= NP) {
+#pragma unroll 8
+        for (int c = r0; c < r1; ++c) g += part[(long long)c * (NP + 1) + k];
+    }
+    s[run][threadIdx.x & 63] = g;
+    __syncthreads();
+    const int t = threadIdx.x & 63;
+    return (s[0][t] + s[1][t]) + (s[2][t] + s[3][t]);
 }
 
-// One Adam step from the chunk partials; loss_log[epoch] += batch loss * w.
-__global__ __launch_bounds__(256) void k_adam(const float *part, int nchunks, float *P, float *m, float *v, float lr,
+// Gradient and loss from the block partials.
+__global__ __launch_bounds__(256) void k_grad_sum(const float *part, int rows, float *grad, float *loss) {
+    const int k = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float g = row_sum(part, rows, k);
+    if (threadIdx.x >= 64 || k > NP) return;
+    if (k == NP) *loss = g;
+    else grad[k] = g;
+}
+
+// One Adam step from the block partials; loss_log[epoch] += batch loss * w.
+__global__ __launch_bounds__(256) void k_adam(const float *part, int rows, float *P, float *m, float *v, float lr,
                                               float bc1, float bc2, float *loss_log, int epoch, float w) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k > NP) return;
-    float g = 0.0f;
-    for (int c = 0; c < nchunks; ++c) g += part[(long long)c * (NP + 1) + k];
+    const int k = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float g = row_sum(part, rows, k);
+    if (threadIdx.x >= 64 || k > NP) return;
     if (k == NP) {
         loss_log[epoch] += g * w;
         return;
@@ -422,16 +481,23 @@ __global__ __launch_bounds__(256) void k_adam(const float *part, int nchunks, fl
     v[k] = vk;
     P[k] -= lr * (mk / bc1) / (sqrtf(vk / bc2) + 1e-8f);
 }
+constexpr int kParamBlocks = (NP + 1 + 63) / 64;
 }  // namespace lbmd
 
 namespace {
 struct TrainScratch {
-    float *act = nullptr, *loss = nullptr, *part = nullptr, *m = nullptr, *v = nullptr;
+    float *p = nullptr;
     ~TrainScratch() {
-        for (float *p : {act, loss, part, m, v})
-            if (p) (void)hipFree(p);
+        if (p) (void)hipFree(p);
     }
 };
+
+// Blocks of k_train: one per 128 samples up to 256, and at most 2048 samples a
+// wave beyond (the length of the FP32 sums over samples).
+int train_blocks(long long n) {
+    const long long b = (n + kTrainSamples - 1) / kTrainSamples;
+    return (int)std::min(b, std::max(256ll, n / 8192));
+}
 }  // namespace
 
 extern "C" lbm_status lbm_mlp_grad(const float *params_dev, const float *feat_dev, const float *target_dev, int64_t n,
@@ -439,28 +505,21 @@ extern "C" lbm_status lbm_mlp_grad(const float *params_dev, const float *feat_de
     if (!params_dev || !feat_dev || !target_dev || !grad_dev || !loss_dev || n < 1)
         return lbmd_set_err(LBM_EINVAL, "bad arguments to lbm_mlp_grad");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    constexpr int SUB = 65536, CHUNK = 1024;
-    const long long nsub = (n + SUB - 1) / SUB;
-    const long long nchunks = nsub * (SUB / CHUNK);
+    // sub-ranges of 2^30 samples (32-bit counts in the kernel), each with its own rows
+    constexpr long long SUB = 1ll << 30;
+    int rows = 0;
+    for (long long b = 0; b < n; b += SUB) rows += train_blocks(std::min<long long>(SUB, n - b));
     TrainScratch sc;
-    HIPCHK(nullptr, hipMalloc(&sc.act, (size_t)SUB * ACT * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.loss, (size_t)SUB * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.part, (size_t)nchunks * (NP + 1) * sizeof(float)));
-    const long long npart = nchunks * (NP + 1);
-    k_zero<<<(unsigned)((npart + 255) / 256), 256, 0, st>>>(sc.part, npart);
-    const float scale = 1.0f / (float)n;
-    for (long long sb = 0; sb < nsub; ++sb) {
-        const long long base = sb * SUB;
-        const int nb = (int)std::min<long long>(SUB, n - base);
-        k_fwd_bwd<<<(nb + 255) / 256, 256, 0, st>>>(params_dev, feat_dev, target_dev, nullptr, base, nb, n,
-                                                   scale, sc.act, sc.loss);
-        const dim3 g((NP + 1 + 255) / 256, (nb + CHUNK - 1) / CHUNK);
-        k_grad_partial<<<g, 256, 0, st>>>(sc.act, sc.loss, nb, CHUNK, sc.part + sb * (SUB / CHUNK) * (NP + 1));
+    HIPCHK(nullptr, hipMalloc(&sc.p, (size_t)rows * (NP + 1) * sizeof(float)));
+    int row = 0;
+    for (long long b = 0; b < n; b += SUB) {
+        const int nb = (int)std::min<long long>(SUB, n - b), blocks = train_blocks(nb);
+        k_train<<<blocks, 256, 0, st>>>(params_dev, feat_dev, target_dev, nullptr, b, nb, n, 1.0f / (float)n,
+                                        sc.p + (long long)row * (NP + 1));
+        row += blocks;
     }
-    k_grad_sum<<<(NP + 1 + 255) / 256, 256, 0, st>>>(sc.part, (int)nchunks, sc.act);
+    k_grad_sum<<<kParamBlocks, 256, 0, st>>>(sc.p, rows, grad_dev, loss_dev);
     HIPCHK(nullptr, hipGetLastError());
-    HIPCHK(nullptr, hipMemcpyAsync(grad_dev, sc.act, NP * sizeof(float), hipMemcpyDeviceToDevice, st));
-    HIPCHK(nullptr, hipMemcpyAsync(loss_dev, sc.act + NP, sizeof(float), hipMemcpyDeviceToDevice, st));
     HIPCHK(nullptr, hipStreamSynchronize(st));
     return LBM_OK;
 }
@@ -472,35 +531,26 @@ extern "C" lbm_status lbm_mlp_train(float *params_dev, const float *feat_dev, co
         batch > 65536 || epochs < 0 || !(lr > 0.0))
         return lbmd_set_err(LBM_EINVAL, "bad arguments to lbm_mlp_train");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    constexpr int CHUNK = 256;
-    const int maxchunks = (batch + CHUNK - 1) / CHUNK;
+    // Adam's two moments, then the block partials
     TrainScratch sc;
-    HIPCHK(nullptr, hipMalloc(&sc.act, (size_t)batch * ACT * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.loss, (size_t)batch * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.part, (size_t)maxchunks * (NP + 1) * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.m, NP * sizeof(float)));
-    HIPCHK(nullptr, hipMalloc(&sc.v, NP * sizeof(float)));
-    k_zero<<<(NP + 255) / 256, 256, 0, st>>>(sc.m, NP);
-    k_zero<<<(NP + 255) / 256, 256, 0, st>>>(sc.v, NP);
+    HIPCHK(nullptr, hipMalloc(&sc.p, (size_t)(2 * NP + train_blocks(batch) * (NP + 1)) * sizeof(float)));
+    float *m = sc.p, *v = m + NP, *part = v + NP;
+    k_zero<<<(2 * NP + 255) / 256, 256, 0, st>>>(m, 2 * NP);
     k_zero<<<(unsigned)((epochs + 255) / 256 + 1), 256, 0, st>>>(loss_log_dev, epochs);
     const long long nbatches = (n + batch - 1) / batch;
     long long step = 0;
     for (int ep = 0; ep < epochs; ++ep) {
         for (long long bi = 0; bi < nbatches; ++bi) {
             const long long base = bi * batch;
-            const int nb = (int)std::min<long long>(batch, n - base);
-            const int nch = (nb + CHUNK - 1) / CHUNK;
-            k_fwd_bwd<<<(nb + 255) / 256, 256, 0, st>>>(params_dev, feat_dev, target_dev,
-                                                       reinterpret_cast<const long long *>(perm_dev),
-                                                       (long long)ep * n + base, nb, n, 1.0f / nb, sc.act,
-                                                       sc.loss);
-            const dim3 g((NP + 1 + 255) / 256, nch);
-            k_grad_partial<<<g, 256, 0, st>>>(sc.act, sc.loss, nb, CHUNK, sc.part);
+            const int nb = (int)std::min<long long>(batch, n - base), rows = train_blocks(nb);
+            k_train<<<rows, 256, 0, st>>>(params_dev, feat_dev, target_dev,
+                                          reinterpret_cast<const long long *>(perm_dev), (long long)ep * n + base, nb,
+                                          n, 1.0f / nb, part);
             ++step;
             const float bc1 = 1.0f - std::pow(0.9f, (float)step);
             const float bc2 = 1.0f - std::pow(0.999f, (float)step);
-            k_adam<<<(NP + 1 + 255) / 256, 256, 0, st>>>(sc.part, nch, params_dev, sc.m, sc.v, (float)lr, bc1, bc2,
-                                                        loss_log_dev, ep, 1.0f / (float)nbatches);
+            k_adam<<<kParamBlocks, 256, 0, st>>>(part, rows, params_dev, m, v, (float)lr, bc1, bc2, loss_log_dev, ep,
+                                                 1.0f / (float)nbatches);
         }
         HIPCHK(nullptr, hipGetLastError());
     }
