@@ -375,7 +375,9 @@ __device__ __forceinline__ void collide_closure(const C (&h)[Q], int tag, bool l
     });
 }
 
-// BGK and BGK + Smagorinsky, population by population: with cu = c.u,
+// BGK and BGK + Smagorinsky of FP16-stored lattices, population by population (their
+// steps are limited by instruction issue; 256^3 D3Q27 two at a time: 290 us a step
+// against 500 with collide_pairs, whose registers spill there): with cu = c.u,
 //   t = drho - 3/2 rho u.u + 9/2 rho cu^2,  feq_k = w (t + 3 rho cu),  feq_k' = w (t - 3 rho cu)
 //   h* = h - omega (h - feq)  (+ Guo terms, skipped as a block without a body force)
 // The Smagorinsky rate takes the momentum flux from the second moment of h less
@@ -458,14 +460,18 @@ __device__ __forceinline__ void collide_bgk(const C (&h)[Q], int tag, const Step
     }
 }
 
-// Two-relaxation-time update for lattices whose fluid nodes all use it, pair by
-// pair: h* = h - omega+ (even part of h - heq) -+ omega- (odd part), plus the Guo
-// terms.  Every product-sum is an explicit fused multiply-add,
-// so the rounding does not depend on the kernel around it.
-// FORCE: the Guo terms are compiled in.  Without a body force they are exactly
-// zero, so both forms give the same result.
-template <int Q, typename C, bool FORCE>
-__device__ __forceinline__ void collide_trt(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q]) {
+// BGK, BGK + Smagorinsky and two-relaxation-time updates for lattices whose fluid
+// nodes use only these, pair by pair: h* = h - omega+ (even part of h - heq) -+
+// omega- (odd part), plus the Guo terms.  The same sums and products, in the same
+// order and fused the same way, as the general update above compiles to in FP32;
+// every product-sum here is an explicit fused multiply-add, so the rounding does
+// not depend on the kernel around it (steps in place and two at a time agree bit
+// for bit).  FORCE: the Guo terms are compiled in.  Without a body force they are
+// exactly zero, so both forms give the same result.  TAGGED: untagged D3Q19 BGK and
+// TRT lattices add u.u and u.F from x on, all others from y on (the order their
+// kernels always had).
+template <int Q, typename C, int MS, bool TAGGED, bool FORCE>
+__device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q]) {
     constexpr int H = (Q - 1) / 2;
     auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
     C drho = C(0), px = C(0), py = C(0), pz = C(0);
@@ -482,16 +488,17 @@ __device__ __forceinline__ void collide_trt(const C (&h)[Q], int tag, const Step
     });
     const C Fx = (C)p.force[0], Fy = (C)p.force[1], Fz = (C)p.force[2];
     const C rho = (C)p.rho0 + drho;
-    const C inv_rho = C(1) / rho;
-    px = fm(C(0.5), Fx, px);
-    py = fm(C(0.5), Fy, py);
-    pz = fm(C(0.5), Fz, pz);
+    C inv_rho = C(1) / rho;
+    if constexpr (FORCE) {
+        px = fm(C(0.5), Fx, px);
+        py = fm(C(0.5), Fy, py);
+        pz = fm(C(0.5), Fz, pz);
+    }
     const C ux = px * inv_rho, uy = py * inv_rho, uz = pz * inv_rho;
-    const C uu = fm(uz, uz, fm(ux, ux, uy * uy));
-    const C wp = (C)p.omega, wm = tag == LBM_TAG_TRT ? (C)p.omega_minus : (C)p.omega;
-    const C uu15 = C(-1.5) * uu;
-    hs[0] = fm(-fm(C(-V<Q, 0>::w), fm(C(-1.5) * rho, uu, drho), h[0]), wp, h[0]);
-    // c.u of pair k
+    constexpr bool kFromX = Q == 19 && !TAGGED && (MS == MS_BGK || MS == MS_TRT);
+    const C uu = fm(uz, uz, kFromX ? fm(uy, uy, ux * ux) : fm(ux, ux, uy * uy));
+    C uu15 = C(-1.5) * uu;
+    // c.u and the even part of the equilibrium of pair k
     auto cu_of = [&](auto K) {
         using Vk = V<Q, decltype(K)::value>;
         C cu = C(0);
@@ -500,43 +507,74 @@ __device__ __forceinline__ void collide_trt(const C (&h)[Q], int tag, const Step
         if constexpr (Vk::z != 0) cu = Vk::x == 0 && Vk::y == 0 ? C(Vk::z) * uz : fm(C(Vk::z) * pz, inv_rho, cu);
         return cu;
     };
-    auto pairs = [&](auto force_c) {
-        constexpr bool kForce = decltype(force_c)::value;
-        C gp = C(0), gm = C(0), uF3 = C(0);
-        if constexpr (kForce) {
-            gp = fm(wp, C(-0.5), C(1));
-            gm = fm(wm, C(-0.5), C(1));
-            const C uF = fm(uz, Fz, fm(ux, Fx, uy * Fy));
-            uF3 = C(-3) * uF;
-            hs[0] = fm(gp, C(-3.0 * V<Q, 0>::w) * uF, hs[0]);
-        }
+    auto ev_of = [&](auto K, C cu) {
+        return C(V<Q, decltype(K)::value>::w) * fm(rho, fm(cu, C(4.5) * cu, uu15), drho);
+    };
+    C wp = (C)p.omega, wm = (C)p.omega;
+    if constexpr ((MS & MS_TRT) != 0) {
+        if (tag == LBM_TAG_TRT) wm = (C)p.omega_minus;
+    }
+    if constexpr ((MS & MS_SMAG) != 0) {
+        C pxx = C(0), pyy = C(0), pzz = C(0), pxy = C(0), pxz = C(0), pyz = C(0);
         sfor<H>([&](auto K) {
-#pragma clang fp contract(off)  // A and B are rounded before they are added
             constexpr int k = decltype(K)::value + 1;
             using Vk = V<Q, k>;
-            const C cu = cu_of(std::integral_constant<int, k>{});
-            const C ev = C(Vk::w) * fm(rho, fm(cu, C(4.5) * cu, uu15), drho);
-            const C od = (C(3.0 * Vk::w) * rho) * cu;
-            C A = -(fm(h[k] + h[k + H], C(0.5), -ev) * wp);
-            C B = -(fm(h[k] - h[k + H], C(0.5), -od) * wm);
-            if constexpr (kForce) {
-                C cF = C(0);
-                if constexpr (Vk::x != 0) cF += C(Vk::x) * Fx;
-                if constexpr (Vk::y != 0) cF += C(Vk::y) * Fy;
-                if constexpr (Vk::z != 0) cF += C(Vk::z) * Fz;
-                A = fm(gp, C(Vk::w) * fm(cF, C(9) * cu, uF3), A);
-                B = fm(C(3.0 * Vk::w) * cF, gm, B);
-            }
-            hs[k] = (h[k] + A) + B;
-            hs[k + H] = (h[k + H] + A) - B;
+            const std::integral_constant<int, k> kc{};
+            const C ne = fm(C(-2), ev_of(kc, cu_of(kc)), h[k] + h[k + H]);
+            if constexpr (Vk::x != 0) pxx += ne;
+            if constexpr (Vk::y != 0) pyy += ne;
+            if constexpr (Vk::z != 0) pzz += ne;
+            if constexpr (Vk::x * Vk::y != 0) pxy += C(Vk::x * Vk::y) * ne;
+            if constexpr (Vk::x * Vk::z != 0) pxz += C(Vk::x * Vk::z) * ne;
+            if constexpr (Vk::y * Vk::z != 0) pyz += C(Vk::y * Vk::z) * ne;
         });
-    };
-    pairs(std::integral_constant<bool, FORCE>{});
+        const C qn = sqrt(fm(C(2), fm(pyz, pyz, fm(pxy, pxy, pxz * pxz)), fm(pzz, pzz, fm(pxx, pxx, pyy * pyy))));
+        const C tau0 = (C)p.tau;
+        const C tau_s = C(0.5) * (tau0 + sqrt(fm(tau0, tau0, (qn * (C)p.smag_c) * inv_rho)));
+        if (tag == LBM_TAG_BGK_SMAG) {
+            wp = C(1) / tau_s;
+            wm = wp;
+        }
+    }
+    // in the two-step kernel, whose registers are short: form the equilibria again
+    // rather than keep them from the momentum flux
+    if constexpr (!FORCE && (MS & MS_SMAG) != 0) asm("" : "+v"(inv_rho), "+v"(uu15));
+    hs[0] = fm(-fm(C(-V<Q, 0>::w), fm(C(-1.5) * rho, uu, drho), h[0]), wp, h[0]);
+    C gp = C(0), gm = C(0), uF3 = C(0);
+    if constexpr (FORCE) {
+        gp = fm(wp, C(-0.5), C(1));
+        gm = fm(wm, C(-0.5), C(1));
+        const C uF = fm(uz, Fz, kFromX ? fm(uy, Fy, ux * Fx) : fm(ux, Fx, uy * Fy));
+        uF3 = C(-3) * uF;
+        hs[0] = fm(gp, C(-3.0 * V<Q, 0>::w) * uF, hs[0]);
+    }
+    sfor<H>([&](auto K) {
+#pragma clang fp contract(off)  // A and B are rounded before they are added
+        constexpr int k = decltype(K)::value + 1;
+        using Vk = V<Q, k>;
+        const std::integral_constant<int, k> kc{};
+        const C cu = cu_of(kc);
+        const C ev = ev_of(kc, cu);
+        const C od = (C(3.0 * Vk::w) * rho) * cu;
+        C A = -(fm(h[k] + h[k + H], C(0.5), -ev) * wp);
+        C B = -(fm(h[k] - h[k + H], C(0.5), -od) * wm);
+        if constexpr (FORCE) {
+            C cF = C(0);
+            if constexpr (Vk::x != 0) cF += C(Vk::x) * Fx;
+            if constexpr (Vk::y != 0) cF += C(Vk::y) * Fy;
+            if constexpr (Vk::z != 0) cF += C(Vk::z) * Fz;
+            A = fm(gp, C(Vk::w) * fm(cF, C(9) * cu, uF3), A);
+            B = fm(C(3.0 * Vk::w) * cF, gm, B);
+        }
+        hs[k] = (h[k] + A) + B;
+        hs[k + H] = (h[k + H] + A) - B;
+    });
 }
 
 // Regularized / recursive-regularized lattices take the moment-only update
 // (collide_regularized).
-template <int Q, typename C, int MS, bool FORCE = true>
+// P: storage precision.
+template <int Q, int P, typename C, int MS, bool TAGGED, bool FORCE = true>
 __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live, const StepParams &p, C (&hs)[Q]) {
     if constexpr (MS == MS_STREAM) {
         // collision switched off: the step only streams (and bounces back)
@@ -547,12 +585,12 @@ __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live
         collide_regularized<Q, C, MS>(h, tag, p, hs);
         return;
     }
-    if constexpr (MS == MS_BGK || MS == (MS_BGK | MS_SMAG)) {
+    if constexpr (P == 2 && (MS == MS_BGK || MS == (MS_BGK | MS_SMAG))) {
         collide_bgk<Q, C, MS>(h, tag, p, hs);
         return;
     }
-    if constexpr (MS == MS_TRT) {
-        collide_trt<Q, C, FORCE>(h, tag, p, hs);
+    if constexpr (MS == MS_BGK || MS == MS_TRT || MS == (MS_BGK | MS_SMAG)) {
+        collide_pairs<Q, C, MS, TAGGED, FORCE>(h, tag, p, hs);
         return;
     }
     if constexpr (MS == (MS_BGK | MS_SMAG | MS_MLP)) {
@@ -968,7 +1006,7 @@ __global__ __launch_bounds__(256) void k_collide_stream(StepParams p) {
 
         if constexpr (MODE != MODE_REDUCE) {
             C hs[Q];
-            collide_node<Q, C, MS>(h, tag, live, p, hs);
+            collide_node<Q, P, C, MS, TAGGED>(h, tag, live, p, hs);
 
             // moving-wall term where x + c_i is a moving wall (nodes next to one only)
             if constexpr (TAGGED && WALLS) {
@@ -1140,7 +1178,7 @@ __global__ __launch_bounds__(256) void k_collide_pair_even(StepParams p) {
             constexpr int i = decltype(I)::value;
             h[i] = k == 0 ? half_lo(u[i]) : half_hi(u[i]);
         });
-        collide_node<Q, C, MS>(h, tag, true, p, hs);
+        collide_node<Q, 2, C, MS, false>(h, tag, true, p, hs);
         sfor<Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (k == 0) o[i] = half_bits(hs[i]);
