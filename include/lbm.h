@@ -279,8 +279,8 @@ lbm_status lbm_reduce(lbm_lattice *lat, lbm_moments *out);
  * eighth-order centred difference (coefficients 4/5, -1/5, 4/105, -1/280 at
  * distances 1..4) on the periodic lattice, u from lbm_read_fields' definition.
  * Needs an all-fluid lattice with every axis >= 9 nodes (EUNSUPPORTED
- * otherwise; the stencil is undefined across walls).  Uses a temporary device
- * buffer of 4 doubles per node.  Synchronizes. */
+ * otherwise; the stencil is undefined across walls).  Uses a device workspace of
+ * 4 doubles per node (the handle's, where it has one that large).  Synchronizes. */
 lbm_status lbm_enstrophy(lbm_lattice *lat, double *out);
 
 /* Wait for all work queued on the handle's stream. */

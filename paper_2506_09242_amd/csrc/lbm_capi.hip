@@ -62,6 +62,8 @@ struct lbm_lattice {
     bool pair = false;              // FP16 even step with two nodes per lane (k_collide_pair_even)
     int tiles_x = 1, tiles_y = 1, n_tiles = 1;
     void *d_pops2 = nullptr;        // second population array (two-step kernel), else null
+    void *d_scratch = nullptr;      // kept workspace of the diagnostics (see Scratch)
+    size_t scratch_bytes = 0;
     bool two = false;               // steps by fours through the two-step kernel
     TwoTiles two_tiles{};
     long long n_fluid = 0;
@@ -96,13 +98,15 @@ struct Launchers {
     hipError_t (*init)(const AuxParams &, hipStream_t);
     hipError_t (*gather)(const AuxParams &, int, hipStream_t);
     hipError_t (*scatter)(const AuxParams &, hipStream_t);
+    hipError_t (*filter)(const AuxParams &, int, double *, hipStream_t);
     hipError_t (*face)(const AuxParams &, int, int, void *, hipStream_t);
     hipError_t (*two)(const StepParams &, void *, const TwoTiles &, int, bool, int, hipStream_t);
 };
 
 template <int Q, int P>
 Launchers make_launchers() {
-    return {&launch_step<Q, P>, &launch_init<Q, P>, &launch_gather<Q, P>, &launch_scatter<Q, P>, &launch_face<Q, P>,
+    return {&launch_step<Q, P>, &launch_init<Q, P>, &launch_gather<Q, P>, &launch_scatter<Q, P>, &launch_filter<Q, P>,
+            &launch_face<Q, P>,
             &launch_two_steps<Q, P>};
 }
 
@@ -328,6 +332,7 @@ AuxParams aux_params(const lbm_lattice *L) {
     a.nz = L->cfg.nz;
     a.lay = make_layout(L->brick ? 1 : 0, L->cfg.nx, L->cfg.ny);
     a.parity = L->parity;
+    a.all_fluid = L->n_fluid == L->ncell ? 1 : 0;
     a.rho0 = L->cfg.rho0;
     for (int k = 0; k < 3; ++k) a.force[k] = L->cfg.force[k];
     return a;
@@ -340,10 +345,40 @@ long long chunk_cells(const lbm_lattice *L, int per_cell_doubles) {
     return std::min<long long>(cap, L->cfg.nz) * plane;
 }
 
-struct DevBuf {
+// Device workspace of one call, used on the lattice's stream: the second
+// population array where it is large enough (no call leaves anything in it), else
+// a workspace that the lattice keeps up to a quarter of its populations' size, else
+// an allocation for the call.  (Allocating and freeing 580 MB took 14 ms a call.)
+struct Scratch {
     void *p = nullptr;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
+    bool own = false;
+    hipError_t get(lbm_lattice *L, size_t bytes) {
+        const size_t pop_bytes = (size_t)L->n_elems * elem_bytes(L->cfg.prec);
+        if (L->d_pops2 && bytes <= pop_bytes) {
+            p = L->d_pops2;
+            return hipSuccess;
+        }
+        if (bytes <= pop_bytes / 4 + (1u << 20)) {
+            if (bytes > L->scratch_bytes) {
+                // the free waits for the work that uses the old one
+                if (L->d_scratch) (void)hipFree(L->d_scratch);
+                L->d_scratch = nullptr;
+                L->scratch_bytes = 0;
+                const hipError_t e = hipMalloc(&L->d_scratch, bytes);
+                if (e != hipSuccess) {
+                    L->d_scratch = nullptr;
+                    return e;
+                }
+                L->scratch_bytes = bytes;
+            }
+            p = L->d_scratch;
+            return hipSuccess;
+        }
+        own = true;
+        return hipMalloc(&p, bytes);
+    }
+    ~Scratch() {
+        if (own && p) (void)hipFree(p);
     }
 };
 }  // namespace
@@ -739,6 +774,7 @@ extern "C" void lbm_destroy(lbm_lattice *lat) {
     if (lat->stream || lat->d_pops) (void)hipStreamSynchronize(lat->stream);
     if (lat->own_pops && lat->d_pops) (void)hipFree(lat->d_pops);
     if (lat->d_pops2) (void)hipFree(lat->d_pops2);
+    if (lat->d_scratch) (void)hipFree(lat->d_scratch);
     if (lat->d_tags) (void)hipFree(lat->d_tags);
     if (lat->d_wall) (void)hipFree(lat->d_wall);
     if (lat->d_partials) (void)hipFree(lat->d_partials);
@@ -803,8 +839,8 @@ extern "C" lbm_status lbm_init_equilibrium(lbm_lattice *lat, const double *rho_h
     CHECK_HANDLE(lat);
     const long long N = lat->ncell;
     const long long chunk = chunk_cells(lat, 4);
-    DevBuf buf;
-    HIPCHK(lat, hipMalloc(&buf.p, (size_t)chunk * 4 * sizeof(double)));
+    Scratch buf;
+    HIPCHK(lat, buf.get(lat, (size_t)chunk * 4 * sizeof(double)));
     double *d = static_cast<double *>(buf.p);
     const Launchers Lc = pick(lat->cfg.q, lat->cfg.prec);
     for (long long c0 = 0; c0 < N; c0 += chunk) {
@@ -1021,8 +1057,8 @@ extern "C" lbm_status lbm_reduce(lbm_lattice *lat, lbm_moments *out) {
 static lbm_status gather_range(lbm_lattice *lat, int gmode, double *host, int per_cell, int shifted) {
     const long long N = lat->ncell;
     const long long chunk = chunk_cells(lat, per_cell);
-    DevBuf buf;
-    HIPCHK(lat, hipMalloc(&buf.p, (size_t)chunk * per_cell * sizeof(double)));
+    Scratch buf;
+    HIPCHK(lat, buf.get(lat, (size_t)chunk * per_cell * sizeof(double)));
     double *d = static_cast<double *>(buf.p);
     const Launchers Lc = pick(lat->cfg.q, lat->cfg.prec);
     for (long long c0 = 0; c0 < N; c0 += chunk) {
@@ -1080,8 +1116,8 @@ extern "C" lbm_status lbm_read_cells(lbm_lattice *lat, const int64_t *cells_host
         if (cells_host[k] < 0 || cells_host[k] >= lat->ncell)
             return set_err(LBM_EINVAL, "cell index %lld out of range", (long long)cells_host[k]);
     const int q = lat->cfg.q;
-    DevBuf buf;
-    HIPCHK(lat, hipMalloc(&buf.p, (size_t)n * (q + 1) * sizeof(double)));
+    Scratch buf;
+    HIPCHK(lat, buf.get(lat, (size_t)n * (q + 1) * sizeof(double)));
     long long *dc = static_cast<long long *>(buf.p);
     double *dout = reinterpret_cast<double *>(dc + n);
     HIPCHK(lat, hipMemcpyAsync(dc, cells_host, (size_t)n * sizeof(int64_t), hipMemcpyHostToDevice, lat->stream));
@@ -1113,8 +1149,8 @@ static lbm_status scatter_range(lbm_lattice *lat, const double *f_host, int64_t 
     const int q = lat->cfg.q;
     const long long N = lat->ncell;
     const long long chunk = chunk_cells(lat, q);
-    DevBuf buf;
-    HIPCHK(lat, hipMalloc(&buf.p, (size_t)chunk * q * sizeof(double)));
+    Scratch buf;
+    HIPCHK(lat, buf.get(lat, (size_t)chunk * q * sizeof(double)));
     double *d = static_cast<double *>(buf.p);
     const Launchers Lc = pick(q, lat->cfg.prec);
     for (long long c0 = 0; c0 < N; c0 += chunk) {
@@ -1162,22 +1198,20 @@ extern "C" lbm_status lbm_enstrophy(lbm_lattice *lat, double *out) {
     if (c.nx < 9 || c.ny < 9 || c.nz < 9) return set_err(LBM_EUNSUPPORTED, "enstrophy needs every axis >= 9 nodes");
     const long long N = lat->ncell;
     const long long nblocks = (N + 255) / 256;
-    DevBuf fields, part, res;
-    HIPCHK(lat, hipMalloc(&fields.p, (size_t)N * 4 * sizeof(double)));
-    HIPCHK(lat, hipMalloc(&part.p, (size_t)nblocks * NRED * sizeof(double)));
-    HIPCHK(lat, hipMalloc(&res.p, NRED * sizeof(double)));
+    // fields (4 planes), block partials, result
+    Scratch buf;
+    HIPCHK(lat, buf.get(lat, ((size_t)N * 4 + (size_t)nblocks * NRED + NRED) * sizeof(double)));
+    double *fields = static_cast<double *>(buf.p), *part = fields + N * 4, *res = part + nblocks * NRED;
     AuxParams a = aux_params(lat);
     a.cell0 = 0;
     a.count = N;
-    a.out = static_cast<double *>(fields.p);
+    a.out = fields;
     HIPCHK(lat, pick(c.q, c.prec).gather(a, G_FIELDS, lat->stream));
-    k_enstrophy<<<(unsigned)nblocks, 256, 0, lat->stream>>>(static_cast<const double *>(fields.p), c.nx, c.ny, c.nz,
-                                                            static_cast<double *>(part.p), nblocks);
+    k_enstrophy<<<(unsigned)nblocks, 256, 0, lat->stream>>>(fields, c.nx, c.ny, c.nz, part, nblocks);
     HIPCHK(lat, hipGetLastError());
-    HIPCHK(lat, launch_finalize(static_cast<const double *>(part.p), nblocks, (int)nblocks, lat->d_stage1,
-                                static_cast<double *>(res.p), lat->stream));
+    HIPCHK(lat, launch_finalize(part, nblocks, (int)nblocks, lat->d_stage1, res, lat->stream));
     double h[NRED];
-    HIPCHK(lat, hipMemcpyAsync(h, res.p, sizeof h, hipMemcpyDeviceToHost, lat->stream));
+    HIPCHK(lat, hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, lat->stream));
     HIPCHK(lat, hipStreamSynchronize(lat->stream));
     *out = h[0] / (double)N;
     return LBM_OK;
@@ -1197,13 +1231,17 @@ void lbmd_clear_mlp(lbm_lattice *lat) {
     lat->d_mlp = nullptr;
     lat->has_mlp = false;
 }
-// Natural-state gather of the whole lattice into device memory (FP64,
-// `per_cell` = 4 fields: rho, ux, uy, uz as planes).  Used by the filter.
-lbm_status lbmd_fields_device(lbm_lattice *lat, double *d_out) {
-    AuxParams a = aux_params(lat);
-    a.cell0 = 0;
-    a.count = lat->ncell;
-    a.out = d_out;
-    HIPCHK(lat, pick(lat->cfg.q, lat->cfg.prec).gather(a, G_FIELDS, lat->stream));
+// Box filter of the natural state by factor^3 and the closure samples of its coarse
+// nodes, then a wait.
+lbm_status lbmd_filter(lbm_lattice *lat, int factor, lbm_status (*targets)(lbm_lattice *, const double *, int, void *),
+                       void *arg) {
+    const long long nc = lat->ncell / ((long long)factor * factor * factor);
+    Scratch coarse;
+    HIPCHK(lat, coarse.get(lat, (size_t)nc * kCoarsePlanes * sizeof(double)));
+    HIPCHK(lat, pick(lat->cfg.q, lat->cfg.prec)
+                    .filter(aux_params(lat), factor, static_cast<double *>(coarse.p), lat->stream));
+    const lbm_status s = targets(lat, static_cast<const double *>(coarse.p), factor, arg);
+    if (s != LBM_OK) return s;
+    HIPCHK(lat, hipStreamSynchronize(lat->stream));
     return LBM_OK;
 }

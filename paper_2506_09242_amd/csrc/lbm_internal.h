@@ -107,6 +107,7 @@ struct AuxParams {
     int nx, ny, nz;
     Layout lay;               // storage order of tags and populations
     int parity;               // layout parity of the state (0: natural)
+    int all_fluid;            // every node is fluid: no tag is read
     int shifted;              // gathers/scatters of h_i = f_i - w_i rho0 (not f_i)
     double rho0;
     double force[3];
@@ -118,6 +119,10 @@ struct AuxParams {
     const double *in_f;       // scatter: Q planes of `count`
     double *out;              // gather output
 };
+
+// Fine-lattice sums of one coarse node of the box filter, as planes: mean density,
+// Favre velocity (3), subgrid stress (xx, yy, zz, xy, xz, yz).
+constexpr int kCoarsePlanes = 10;
 
 enum GatherMode : int { G_POPS = 0, G_FIELDS = 1, G_CELLS = 2 };
 
@@ -152,6 +157,9 @@ template <int Q, int P>
 hipError_t launch_gather(const AuxParams &a, int gmode, hipStream_t s);
 template <int Q, int P>
 hipError_t launch_scatter(const AuxParams &a, hipStream_t s);
+// Box filter of factor^3 nodes of the natural state into coarse[kCoarsePlanes][nodes / factor^3].
+template <int Q, int P>
+hipError_t launch_filter(const AuxParams &a, int factor, double *coarse, hipStream_t s);
 // Copy the slots that cross a z face between the lattice and buf (see
 // lbm_face_pack): face 0 = plane 0, directions with c_z = +1; face 1 =
 // plane nz-1, directions with c_z = -1; unpack = 1 copies buf into the lattice.

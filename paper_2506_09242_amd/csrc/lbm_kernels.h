@@ -1273,26 +1273,109 @@ __global__ __launch_bounds__(256) void k_init(AuxParams a) {
     });
 }
 
-// Natural state of the node with natural index n: h_i(n) for every i (slot
-// map of the layout parity).
+// Natural state of the node at (x, y, z): f_i (or h_i) for every i (slot map of
+// the layout parity).
 template <int Q, int P>
-__device__ __forceinline__ void load_natural(const AuxParams &a, long long n, double (&fo)[Q]) {
+__device__ __forceinline__ void load_natural(const AuxParams &a, int x, int y, int z, double (&fo)[Q]) {
     using S = typename Prec<P>::S;
     const S *f = static_cast<const S *>(a.pops);
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((long long)nx * ny));
-    const int sn = a.lay.at(x, y, z);
+    const long long own = pop_base<Q>(a.lay.at(x, y, z));
     sfor<Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         using Vi = V<Q, i>;
-        long long off = pop_base<Q>(sn) + slot_off(i);
+        long long off = own + slot_off(i);
         if (a.parity != 0 && i != 0) {
             const int sx = wrap_idx(x - Vi::x, nx), sy = wrap_idx(y - Vi::y, ny), sz = wrap_idx(z - Vi::z, nz);
             const int src = a.lay.at(sx, sy, sz);
-            if (is_fluid_tag(a.tags[src])) off = pop_base<Q>(src) + slot_off(Vi::opp);
+            if (a.all_fluid || is_fluid_tag(a.tags[src])) off = pop_base<Q>(src) + slot_off(Vi::opp);
         }
         fo[i] = a.shifted ? (double)f[off] : (double)f[off] + Vi::w * a.rho0;
     });
+}
+
+// Density and velocity from the unshifted populations.
+template <int Q>
+__device__ __forceinline__ void node_fields(const AuxParams &a, const double (&fo)[Q], double &rho, double (&u)[3]) {
+    double jx = 0.0, jy = 0.0, jz = 0.0;
+    rho = 0.0;
+    sfor<Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        using Vi = V<Q, i>;
+        rho += fo[i];
+        jx += Vi::x * fo[i];
+        jy += Vi::y * fo[i];
+        jz += Vi::z * fo[i];
+    });
+    const double inv = 1.0 / rho;
+    u[0] = (jx + 0.5 * a.force[0]) * inv;
+    u[1] = (jy + 0.5 * a.force[1]) * inv;
+    u[2] = (jz + 0.5 * a.force[2]) * inv;
+}
+
+// Box filter: a block takes 256 / factor coarse nodes of one coarse row, a thread
+// one fine column of x (every 256th beyond a factor of 256), whose factor^2 nodes it
+// sums; the columns of a coarse node are then added through LDS.  Bound by memory:
+// one read of the populations, where a gather of the fields to FP64 planes and a
+// filter of those moved them to memory and back (256^3 D3Q27 FP32, factor 4, the
+// whole call: 15.1 ms with those and their 580 MB allocated and freed, 0.35 ms now).
+template <int Q, int P>
+__global__ __launch_bounds__(256) void k_filter(AuxParams a, int factor, int cx, int cy, int cz, double *coarse) {
+    __shared__ double s[kCoarsePlanes][256];
+    const int cols = factor < 256 ? factor : 256, per = 256 / cols;  // columns of a coarse node, coarse nodes a block
+    const int segs = (cx + per - 1) / per;
+    const int seg = blockIdx.x % segs, row = blockIdx.x / segs;
+    const int Y = row % cy, Z = row / cy;
+    const int t = threadIdx.x, c = t / cols, xi = t - c * cols;
+    const int X = seg * per + c;
+    double v[kCoarsePlanes] = {};
+    if (c < per && X < cx) {
+        for (int dz = 0; dz < factor; ++dz)
+            for (int dy = 0; dy < factor; ++dy)
+                for (int dx = xi; dx < factor; dx += cols) {
+                    const int x = X * factor + dx, y = Y * factor + dy, z = Z * factor + dz;
+                    if (!a.all_fluid && !is_fluid_tag(a.tags[a.lay.at(x, y, z)])) continue;
+                    double fo[Q], r, u[3];
+                    load_natural<Q, P>(a, x, y, z, fo);
+                    node_fields<Q>(a, fo, r, u);
+                    v[0] += r;
+                    v[1] += r * u[0];
+                    v[2] += r * u[1];
+                    v[3] += r * u[2];
+                    v[4] += r * u[0] * u[0];
+                    v[5] += r * u[1] * u[1];
+                    v[6] += r * u[2] * u[2];
+                    v[7] += r * u[0] * u[1];
+                    v[8] += r * u[0] * u[2];
+                    v[9] += r * u[1] * u[2];
+                }
+    }
+#pragma unroll
+    for (int k = 0; k < kCoarsePlanes; ++k) s[k][t] = v[k];
+    __syncthreads();
+    for (int q = t; q < per * kCoarsePlanes; q += 256) {
+        const int k = q / per, n = q - k * per;
+        double sum = 0.0;
+        for (int j = 0; j < cols; ++j) sum += s[k][n * cols + j];
+        s[k][n * cols] = sum;
+    }
+    __syncthreads();
+    const int Xo = seg * per + t;
+    if (t >= per || Xo >= cx) return;
+    const int e = t * cols;
+    const long long nc = (long long)cx * cy * cz, o = ((long long)Z * cy + Y) * cx + Xo;
+    const double vol = (double)factor * factor * factor, sr = s[0][e];
+    const double Ux = s[1][e] / sr, Uy = s[2][e] / sr, Uz = s[3][e] / sr;
+    coarse[o] = sr / vol;
+    coarse[nc + o] = Ux;
+    coarse[2 * nc + o] = Uy;
+    coarse[3 * nc + o] = Uz;
+    coarse[4 * nc + o] = s[4][e] / sr - Ux * Ux;
+    coarse[5 * nc + o] = s[5][e] / sr - Uy * Uy;
+    coarse[6 * nc + o] = s[6][e] / sr - Uz * Uz;
+    coarse[7 * nc + o] = s[7][e] / sr - Ux * Uy;
+    coarse[8 * nc + o] = s[8][e] / sr - Ux * Uz;
+    coarse[9 * nc + o] = s[9][e] / sr - Uy * Uz;
 }
 
 template <int Q, int P>
@@ -1300,11 +1383,14 @@ __global__ __launch_bounds__(256) void k_gather(AuxParams a, int gmode) {
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
     if (t >= a.count) return;
     const long long n = gmode == G_CELLS ? a.cells[t] : a.cell0 + t;
-    const bool fl = is_fluid_tag(a.tags[storage_index(a, n)]);
+    // n < 2^31 (lbm_config), so 32-bit divisions do
+    const unsigned row = (unsigned)n / (unsigned)a.nx;
+    const int x = (int)((unsigned)n - row * (unsigned)a.nx), y = (int)(row % (unsigned)a.ny), z = (int)(row / (unsigned)a.ny);
+    const bool fl = a.all_fluid || is_fluid_tag(a.tags[a.lay.at(x, y, z)]);
     if (gmode == G_FIELDS) a.shifted = 0;
     double fo[Q];
     if (fl) {
-        load_natural<Q, P>(a, n, fo);
+        load_natural<Q, P>(a, x, y, z, fo);
     } else {
         sfor<Q>([&](auto I) { fo[decltype(I)::value] = 0.0; });
     }
@@ -1313,20 +1399,12 @@ __global__ __launch_bounds__(256) void k_gather(AuxParams a, int gmode) {
     } else if (gmode == G_CELLS) {
         sfor<Q>([&](auto I) { a.out[t * Q + decltype(I)::value] = fo[decltype(I)::value]; });
     } else {
-        double rho = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
-        sfor<Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            using Vi = V<Q, i>;
-            rho += fo[i];
-            jx += Vi::x * fo[i];
-            jy += Vi::y * fo[i];
-            jz += Vi::z * fo[i];
-        });
-        const double inv = fl ? 1.0 / rho : 0.0;
+        double rho = 0.0, u[3] = {0.0, 0.0, 0.0};
+        if (fl) node_fields<Q>(a, fo, rho, u);
         a.out[t] = rho;
-        a.out[a.count + t] = fl ? (jx + 0.5 * a.force[0]) * inv : 0.0;
-        a.out[2 * a.count + t] = fl ? (jy + 0.5 * a.force[1]) * inv : 0.0;
-        a.out[3 * a.count + t] = fl ? (jz + 0.5 * a.force[2]) * inv : 0.0;
+        a.out[a.count + t] = u[0];
+        a.out[2 * a.count + t] = u[1];
+        a.out[3 * a.count + t] = u[2];
     }
 }
 
@@ -1482,6 +1560,15 @@ hipError_t launch_gather(const AuxParams &a, int gmode, hipStream_t s) {
 }
 
 template <int Q, int P>
+hipError_t launch_filter(const AuxParams &a, int factor, double *coarse, hipStream_t s) {
+    const int cx = a.nx / factor, cy = a.ny / factor, cz = a.nz / factor;
+    const int per = 256 / (factor < 256 ? factor : 256);
+    const long long blocks = (long long)((cx + per - 1) / per) * cy * cz;
+    k_filter<Q, P><<<(unsigned)blocks, 256, 0, s>>>(a, factor, cx, cy, cz, coarse);
+    return hipGetLastError();
+}
+
+template <int Q, int P>
 hipError_t launch_scatter(const AuxParams &a, hipStream_t s) {
     const unsigned blocks = (unsigned)((a.count + 255) / 256);
     k_scatter<Q, P><<<blocks, 256, 0, s>>>(a);
@@ -1500,6 +1587,7 @@ hipError_t launch_face(const AuxParams &a, int face, int unpack, void *buf, hipS
     template hipError_t launch_init<Q, P>(const AuxParams &, hipStream_t);                                \
     template hipError_t launch_gather<Q, P>(const AuxParams &, int, hipStream_t);                         \
     template hipError_t launch_scatter<Q, P>(const AuxParams &, hipStream_t);                             \
+    template hipError_t launch_filter<Q, P>(const AuxParams &, int, double *, hipStream_t);               \
     template hipError_t launch_face<Q, P>(const AuxParams &, int, int, void *, hipStream_t);
 
 }  // namespace lbmd

@@ -23,7 +23,8 @@ bool lbmd_failed(const lbm_lattice *lat);
 void lbmd_set_mlp(lbm_lattice *lat, void *block, const MlpDev &m);
 void *lbmd_mlp_block(lbm_lattice *lat);
 void lbmd_clear_mlp(lbm_lattice *lat);
-lbm_status lbmd_fields_device(lbm_lattice *lat, double *d_out);
+lbm_status lbmd_filter(lbm_lattice *lat, int factor, lbm_status (*targets)(lbm_lattice *, const double *, int, void *),
+                       void *arg);
 
 #define HIPCHK(lat, expr)                                              \
     do {                                                               \
@@ -176,46 +177,7 @@ extern "C" lbm_status lbm_mlp_infer(const float *params_host, double nu0, const 
 
 // ------------------------------------------------------------ box filter
 namespace lbmd {
-// fields: FP64 planes rho, ux, uy, uz of the fine lattice.  coarse: FP64
-// planes rho_bar, U (3), T (6: xx yy zz xy xz yz) per coarse node.
-__global__ __launch_bounds__(256) void k_box_filter(const double *fields, long long nfine, int nx, int ny, int fct,
-                                                    int cx, int cy, int cz, double *coarse) {
-    const long long nc = (long long)cx * cy * cz;
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= nc) return;
-    const int X = (int)(t % cx), Y = (int)((t / cx) % cy), Z = (int)(t / ((long long)cx * cy));
-    double sr = 0, sx = 0, sy = 0, sz = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
-    for (int dz = 0; dz < fct; ++dz)
-        for (int dy = 0; dy < fct; ++dy)
-            for (int dx = 0; dx < fct; ++dx) {
-                const long long n = ((long long)(Z * fct + dz) * ny + (Y * fct + dy)) * nx + (X * fct + dx);
-                const double r = fields[n], ux = fields[nfine + n], uy = fields[2 * nfine + n],
-                             uz = fields[3 * nfine + n];
-                sr += r;
-                sx += r * ux;
-                sy += r * uy;
-                sz += r * uz;
-                txx += r * ux * ux;
-                tyy += r * uy * uy;
-                tzz += r * uz * uz;
-                txy += r * ux * uy;
-                txz += r * ux * uz;
-                tyz += r * uy * uz;
-            }
-    const double vol = (double)fct * fct * fct;
-    const double Ux = sx / sr, Uy = sy / sr, Uz = sz / sr;
-    coarse[t] = sr / vol;
-    coarse[nc + t] = Ux;
-    coarse[2 * nc + t] = Uy;
-    coarse[3 * nc + t] = Uz;
-    coarse[4 * nc + t] = txx / sr - Ux * Ux;
-    coarse[5 * nc + t] = tyy / sr - Uy * Uy;
-    coarse[6 * nc + t] = tzz / sr - Uz * Uz;
-    coarse[7 * nc + t] = txy / sr - Ux * Uy;
-    coarse[8 * nc + t] = txz / sr - Ux * Uz;
-    coarse[9 * nc + t] = tyz / sr - Uy * Uz;
-}
-
+// coarse: FP64 planes rho_bar, U (3), T (6: xx yy zz xy xz yz) per coarse node (k_filter).
 __global__ __launch_bounds__(256) void k_closure_targets(const double *coarse, int cx, int cy, int cz, double nu_c,
                                                          float *feat, float *target) {
     const long long nc = (long long)cx * cy * cz;
@@ -270,30 +232,22 @@ extern "C" lbm_status lbm_filter_snapshot(lbm_lattice *fine, int factor, float *
     if (factor < 1 || c.nx % factor || c.ny % factor || c.nz % factor)
         return lbmd_set_err(LBM_EINVAL, "lattice sizes must be divisible by the filter factor");
     if (!feat_dev || !target_dev) return lbmd_set_err(LBM_EINVAL, "null output");
-    const long long N = (long long)c.nx * c.ny * c.nz;
-    const int cx = c.nx / factor, cy = c.ny / factor, cz = c.nz / factor;
-    const long long nc = (long long)cx * cy * cz;
-    hipStream_t st = lbmd_stream(fine);
-    double *d_fields = nullptr, *d_coarse = nullptr;
-    HIPCHK(fine, hipMalloc(&d_fields, (size_t)N * 4 * sizeof(double)));
-    hipError_t e = hipMalloc(&d_coarse, (size_t)nc * 10 * sizeof(double));
-    if (e != hipSuccess) {
-        (void)hipFree(d_fields);
-        return lbmd_fail_hip(fine, e, "hipMalloc coarse");
-    }
-    lbm_status s = lbmd_fields_device(fine, d_fields);
-    if (s == LBM_OK) {
-        const unsigned blocks = (unsigned)((nc + 255) / 256);
-        k_box_filter<<<blocks, 256, 0, st>>>(d_fields, N, c.nx, c.ny, factor, cx, cy, cz, d_coarse);
-        const double nu_c = (c.tau - 0.5) / 3.0 / factor;
-        k_closure_targets<<<blocks, 256, 0, st>>>(d_coarse, cx, cy, cz, nu_c, feat_dev, target_dev);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) s = lbmd_fail_hip(fine, e, "closure filter");
-    }
-    (void)hipFree(d_fields);
-    (void)hipFree(d_coarse);
-    return s;
+    struct Out {
+        float *feat, *target;
+    } out{feat_dev, target_dev};
+    return lbmd_filter(
+        fine, factor,
+        [](lbm_lattice *lat, const double *coarse, int f, void *arg) -> lbm_status {
+            const lbm_config c = lbmd_config(lat);
+            const Out *o = static_cast<const Out *>(arg);
+            const int cx = c.nx / f, cy = c.ny / f, cz = c.nz / f;
+            const double nu_c = (c.tau - 0.5) / 3.0 / f;
+            const unsigned blocks = (unsigned)(((long long)cx * cy * cz + 255) / 256);
+            k_closure_targets<<<blocks, 256, 0, lbmd_stream(lat)>>>(coarse, cx, cy, cz, nu_c, o->feat, o->target);
+            HIPCHK(lat, hipGetLastError());
+            return LBM_OK;
+        },
+        &out);
 }
 
 // ------------------------------------------------------------ training
