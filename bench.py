@@ -584,7 +584,9 @@ def main():
     traffic = stored_traffic(args.workload, main_p)
     roofline = {"bound": "hbm", "achieved": round(m["alg_GBps"], 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(m["alg_GBps"] / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "k_collide_stream (even/odd AA steps, averaged over the timed region)",
+                "kernel": "k_two_steps by fours between samples where the lattice takes it (two steps per pass over "
+                          "memory), else k_collide_stream even/odd; alg_bytes counts one pass per step, so achieved "
+                          "may exceed the peak: traffic is what a step moves",
                 "alg_bytes_per_launch": m["bytes_per_launch"],
                 "even_frac": m.get("even_hbm_frac"), "odd_frac": m.get("odd_hbm_frac")}
 

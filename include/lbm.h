@@ -302,7 +302,9 @@ int64_t lbm_time(const lbm_lattice *lat);
 /* Density and velocity of the natural state at the current time, FP64:
  * rho_host nx*ny*nz, u_host 3*nx*ny*nz (planes ux, uy, uz), each nullable.
  * u = (sum c_i f_i + F/2)/rho.  Non-fluid nodes read 0.  Synchronizes.
- * ENOMEM if the host staging copy cannot be allocated. */
+ * Reads of 8 MB and more go through 16 MB of pinned staging that the handle keeps
+ * and up to eight threads that end before the call returns (lbm_read_populations
+ * and lbm_read_state too). */
 lbm_status lbm_read_fields(lbm_lattice *lat, double *rho_host, double *u_host);
 
 /* All populations f_i (offset added back, FP64, canonical order, natural

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -10,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "lbm.h"
@@ -64,6 +66,7 @@ struct lbm_lattice {
     void *d_pops2 = nullptr;        // second population array (two-step kernel), else null
     void *d_scratch = nullptr;      // kept workspace of the diagnostics (see Scratch)
     size_t scratch_bytes = 0;
+    char *h_staging = nullptr;      // pinned staging of large reads (see copy_out)
     bool two = false;               // steps by fours through the two-step kernel
     TwoTiles two_tiles{};
     long long n_fluid = 0;
@@ -785,6 +788,7 @@ extern "C" void lbm_destroy(lbm_lattice *lat) {
     if (lat->own_pops && lat->d_pops) (void)hipFree(lat->d_pops);
     if (lat->d_pops2) (void)hipFree(lat->d_pops2);
     if (lat->d_scratch) (void)hipFree(lat->d_scratch);
+    if (lat->h_staging) (void)hipHostFree(lat->h_staging);
     if (lat->d_tags) (void)hipFree(lat->d_tags);
     if (lat->d_wall) (void)hipFree(lat->d_wall);
     if (lat->d_partials) (void)hipFree(lat->d_partials);
@@ -1064,7 +1068,101 @@ extern "C" lbm_status lbm_reduce(lbm_lattice *lat, lbm_moments *out) {
 }
 
 // ---------------------------------------------------------------- readback
-static lbm_status gather_range(lbm_lattice *lat, int gmode, double *host, int per_cell, int shifted) {
+// Copies of a chunk's planes to the caller's memory.  A plain copy into pageable
+// memory is bound by the one thread that faults its pages in and copies into them
+// (256^3 fields, 537 MB: 50 ms and more; the link takes 9.4).  From kCopyMin bytes
+// on, threads that last for the chunk take pieces in turn, each through its own
+// pinned piece of staging: the same read 14.5 ms with eight threads and pieces of
+// 2 MB, 16.9 with four threads, 18.3 with pieces of 1 MB; 64^3 fields (8.4 MB) 0.95
+// -> 0.50 ms, below that a plain copy is as fast.  Memory that HIP knows (pinned,
+// managed, device) is copied to directly, and so is everything if there is no
+// staging to be had; a thread that cannot start is done without.
+constexpr size_t kCopyPiece = 2u << 20, kCopyMin = 8u << 20;
+constexpr int kCopyThreads = 8;
+
+struct CopyOut {
+    lbm_lattice *lat;
+    double *const *planes;
+    const double *src;          // device planes of `cnt` doubles
+    int n_planes;
+    long long c0, cnt;          // first node of the chunk in the host planes, nodes in it
+    std::atomic<long long> next{0};
+    std::atomic<int> err{hipSuccess};
+};
+
+static void copy_pieces(CopyOut *c, int worker) {
+    const size_t bytes = (size_t)c->cnt * sizeof(double), per_plane = (bytes + kCopyPiece - 1) / kCopyPiece;
+    char *slot = c->lat->h_staging + (size_t)worker * kCopyPiece;
+    hipEvent_t ev = nullptr;
+    int cur = -1;
+    hipError_t e = hipGetDevice(&cur);
+    if (e == hipSuccess && cur != c->lat->device) e = hipSetDevice(c->lat->device);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventBlockingSync);
+    while (e == hipSuccess && c->err.load() == hipSuccess) {
+        const long long i = c->next.fetch_add(1);
+        const long long k = i / (long long)per_plane;
+        if (k >= c->n_planes) break;
+        if (!c->planes[k]) continue;
+        const size_t off = (size_t)(i - k * per_plane) * kCopyPiece, n = std::min(kCopyPiece, bytes - off);
+        e = hipMemcpyAsync(slot, reinterpret_cast<const char *>(c->src + k * c->cnt) + off, n, hipMemcpyDeviceToHost,
+                           c->lat->stream);
+        if (e == hipSuccess) e = hipEventRecord(ev, c->lat->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(ev);
+        if (e == hipSuccess) std::memcpy(reinterpret_cast<char *>(c->planes[k] + c->c0) + off, slot, n);
+    }
+    if (e != hipSuccess) c->err.store(e);
+    if (ev) (void)hipEventDestroy(ev);
+    if (cur >= 0 && cur != c->lat->device) (void)hipSetDevice(cur);
+}
+
+static hipError_t copy_out(lbm_lattice *L, double *const *planes, int n_planes, const double *src, long long c0,
+                           long long cnt) {
+    const size_t bytes = (size_t)cnt * sizeof(double);
+    size_t total = 0;
+    bool staged = true;
+    for (int k = 0; k < n_planes; ++k) {
+        if (!planes[k]) continue;
+        total += bytes;
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, planes[k] + c0) != hipSuccess)
+            (void)hipGetLastError();  // memory that HIP does not know
+        else if (at.type != hipMemoryTypeUnregistered)
+            staged = false;
+    }
+    staged = staged && total >= kCopyMin;
+    if (staged && !L->h_staging &&
+        hipHostMalloc(reinterpret_cast<void **>(&L->h_staging), kCopyPiece * kCopyThreads, hipHostMallocDefault) !=
+            hipSuccess) {
+        (void)hipGetLastError();
+        L->h_staging = nullptr;
+        staged = false;
+    }
+    if (!staged) {
+        for (int k = 0; k < n_planes; ++k) {
+            if (!planes[k]) continue;
+            const hipError_t e =
+                hipMemcpyAsync(planes[k] + c0, src + k * cnt, bytes, hipMemcpyDeviceToHost, L->stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipStreamSynchronize(L->stream);
+    }
+    CopyOut c{L, planes, src, n_planes, c0, cnt};
+    std::thread th[kCopyThreads - 1];
+    for (int w = 1; w < kCopyThreads; ++w) {
+        try {
+            th[w - 1] = std::thread(copy_pieces, &c, w);
+        } catch (...) {
+            break;  // fewer of them
+        }
+    }
+    copy_pieces(&c, 0);
+    for (std::thread &t : th)
+        if (t.joinable()) t.join();
+    return static_cast<hipError_t>(c.err.load());
+}
+
+// planes: host pointer of each of the per_cell output planes, null where not wanted.
+static lbm_status gather_range(lbm_lattice *lat, int gmode, double *const *planes, int per_cell, int shifted) {
     const long long N = lat->ncell;
     const long long chunk = chunk_cells(lat, per_cell);
     Scratch buf;
@@ -1079,10 +1177,7 @@ static lbm_status gather_range(lbm_lattice *lat, int gmode, double *host, int pe
         a.out = d;
         a.shifted = shifted;
         HIPCHK(lat, Lc.gather(a, gmode, lat->stream));
-        for (int k = 0; k < per_cell; ++k)
-            HIPCHK(lat, hipMemcpyAsync(host + k * N + c0, d + k * cnt, cnt * sizeof(double), hipMemcpyDeviceToHost,
-                                       lat->stream));
-        HIPCHK(lat, hipStreamSynchronize(lat->stream));
+        HIPCHK(lat, copy_out(lat, planes, per_cell, d, c0, cnt));
     }
     return LBM_OK;
 }
@@ -1091,31 +1186,27 @@ extern "C" lbm_status lbm_read_fields(lbm_lattice *lat, double *rho_host, double
     CHECK_HANDLE(lat);
     if (!rho_host && !u_host) return LBM_OK;
     const long long N = lat->ncell;
-    std::vector<double> tmp;
-    double *dst;
-    try {
-        tmp.resize((size_t)N * 4);
-    } catch (...) {
-        return set_err(LBM_ENOMEM, "host allocation failed");
-    }
-    dst = tmp.data();
-    lbm_status st = gather_range(lat, G_FIELDS, dst, 4, 0);
-    if (st != LBM_OK) return st;
-    if (rho_host) std::memcpy(rho_host, dst, (size_t)N * sizeof(double));
-    if (u_host) std::memcpy(u_host, dst + N, (size_t)N * 3 * sizeof(double));
-    return LBM_OK;
+    double *planes[4] = {rho_host, u_host, u_host ? u_host + N : nullptr, u_host ? u_host + 2 * N : nullptr};
+    return gather_range(lat, G_FIELDS, planes, 4, 0);
+}
+
+// All populations (shifted or not) as planes of f_host.
+static lbm_status read_planes(lbm_lattice *lat, double *f_host, int shifted) {
+    double *planes[27];
+    for (int k = 0; k < lat->cfg.q; ++k) planes[k] = f_host + k * lat->ncell;
+    return gather_range(lat, G_POPS, planes, lat->cfg.q, shifted);
 }
 
 extern "C" lbm_status lbm_read_populations(lbm_lattice *lat, double *f_host) {
     CHECK_HANDLE(lat);
     if (!f_host) return set_err(LBM_EINVAL, "null output");
-    return gather_range(lat, G_POPS, f_host, lat->cfg.q, 0);
+    return read_planes(lat, f_host, 0);
 }
 
 extern "C" lbm_status lbm_read_state(lbm_lattice *lat, double *h_host) {
     CHECK_HANDLE(lat);
     if (!h_host) return set_err(LBM_EINVAL, "null output");
-    return gather_range(lat, G_POPS, h_host, lat->cfg.q, 1);
+    return read_planes(lat, h_host, 1);
 }
 
 extern "C" lbm_status lbm_read_cells(lbm_lattice *lat, const int64_t *cells_host, int64_t n, double *f_host) {
