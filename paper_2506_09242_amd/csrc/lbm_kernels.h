@@ -1046,7 +1046,15 @@ __global__ __launch_bounds__(256) void k_collide_stream(StepParams p) {
                         using Vi = V<Q, i>;
                         if constexpr (i > 0) {
                             if ((wall >> i) & 1u) {
-                                const int dst = zo[1 + Vi::z] + yo[1 + Vi::y] + xo[1 + Vi::x];
+                                int dst;
+                                if constexpr (B32) {
+                                    // from the byte offset: three terms to keep, not six
+                                    const unsigned e = nb32(Vi::z, Vi::y, Vi::x, 0) / (unsigned)sizeof(S);
+                                    dst = (int)(((e >> kBlockLog2) / (unsigned)Q << kBlockLog2) |
+                                                (e & (kBlockNodes - 1)));
+                                } else {
+                                    dst = zo[1 + Vi::z] + yo[1 + Vi::y] + xo[1 + Vi::x];
+                                }
                                 const int t = p.tags[dst];
                                 if (t >= LBM_TAG_WALL0) {
                                     const double *uw = p.wall_u + 3 * (t - LBM_TAG_WALL0);
@@ -1087,6 +1095,12 @@ __global__ __launch_bounds__(256) void k_collide_stream(StepParams p) {
                 }
             } else if constexpr (B32) {
                 if (live || filler) *at(f, 0, pn) = (S)hs[0];
+                // the push forms its addresses anew: kept from the pull, the sums hold 14 to
+                // 18 registers across the collision
+                if constexpr (PARITY == 1) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) asm("" : "+v"(px[k]), "+v"(py[k]), "+v"(pz[k]));
+                }
                 // (no odd-step fillers in this layout: its own slots written as well left
                 // 0.3 instead of 1.5 million of the 6.4 million sector writes partial,
                 // and the step where it was, 188.9 us against 188.8)
