@@ -1523,7 +1523,8 @@ __global__ __launch_bounds__(256) void k_face(AuxParams a, int face, int unpack,
 constexpr unsigned kEvenLdsCap = 41u << 10;
 
 // The same for both parities of FP32 brick-layout lattices, at four workgroups a
-// CU: 256^3 porous D3Q19 TRT 190.5 us a step against 197 without a cap.
+// CU: 256^3 porous D3Q19 TRT 188.5 us a step against 195.5 without a cap (five workgroups
+// 191.0, three 191.2).
 constexpr unsigned kBrickLdsCap = 40000u;
 
 template <int Q, int P, int MS, bool TG, int MODE, int ADDR>

@@ -1,7 +1,8 @@
 // lbm_mlp.hip -- learned eddy-viscosity closure: parameter packing, the
 // standalone inference kernel (same device code as the fused collision), the
 // training samples of a filtered fine lattice (its filter is k_filter in
-// lbm_kernels.h), and the FP32 training kernels (forward, backward, deterministic gradient reduction, Adam).
+// lbm_kernels.h), and the FP32 training kernels (forward, backward,
+// deterministic gradient reduction, Adam).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
