@@ -655,7 +655,8 @@ static lbm_status create_impl(const lbm_config *cfg, const uint8_t *tags_host, v
     // small part of what is free, and without it the lattice steps in place.  Not
     // where over a quarter of the nodes are solid (rows of a 144 x 176 x 112 rock of
     // porosity 0.20: 0.85 times as fast as the one-step kernels, which skip solid waves).
-    if (!brick && two_models(ms) && 4 * nf >= 3 * N && plan_two(L, tagged)) {
+    if (!brick && two_built(cfg->q, cfg->prec, ms, tagged, step_params(L).has_force) && 4 * nf >= 3 * N &&
+        plan_two(L, tagged)) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need_bytes <= free_b / 8 &&
             hipMalloc(&L->d_pops2, need_bytes) == hipSuccess)
