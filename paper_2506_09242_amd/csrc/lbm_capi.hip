@@ -1147,6 +1147,11 @@ static hipError_t copy_out(lbm_lattice *L, double *const *planes, int n_planes, 
         }
         return hipStreamSynchronize(L->stream);
     }
+    // The planes are written on the calling thread's view of the stream: a handle made on
+    // hipStreamPerThread names another stream in each thread, whose copies nothing would
+    // order after the gather.
+    const hipError_t ready = hipStreamSynchronize(L->stream);
+    if (ready != hipSuccess) return ready;
     CopyOut c{L, planes, src, n_planes, c0, cnt};
     std::thread th[kCopyThreads - 1];
     for (int w = 1; w < kCopyThreads; ++w) {
