@@ -375,6 +375,16 @@ __device__ __forceinline__ void collide_closure(const C (&h)[Q], int tag, bool l
     });
 }
 
+// A kernel parameter as the two-step kernel uses it.  FRESH ties it to a value of the
+// node, so that what is computed from parameters alone (weights times forces and
+// rates) is formed for each node and not kept in registers across the march over
+// planes: there it is spilled, and its reload waits for the populations in flight.
+template <bool FRESH, typename C>
+__device__ __forceinline__ C node_param(double v, C h) {
+    if constexpr (FRESH) asm("" : "+s"(v) : "v"(h));
+    return (C)v;
+}
+
 // BGK, BGK + Smagorinsky and two-relaxation-time updates for lattices whose fluid
 // nodes use only these, pair by pair: h* = h - omega+ (even part of h - heq) -+
 // omega- (odd part), plus the Guo terms.  The same sums and products, in the same
@@ -386,7 +396,7 @@ __device__ __forceinline__ void collide_closure(const C (&h)[Q], int tag, bool l
 // TRT lattices add u.u and u.F from x on, all others from y on (the order their
 // kernels always had), and so do the even steps of FP16 lattices with two nodes a
 // lane (from_y).
-template <int Q, typename C, int MS, bool TAGGED, bool FORCE>
+template <int Q, typename C, int MS, bool TAGGED, bool FORCE, bool TWO>
 __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q], bool from_y) {
     constexpr int H = (Q - 1) / 2;
     auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
@@ -402,8 +412,13 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
         if constexpr (Vi::z == 1) pz += h[i];
         if constexpr (Vi::z == -1) pz -= h[i];
     });
-    const C Fx = (C)p.force[0], Fy = (C)p.force[1], Fz = (C)p.force[2];
-    const C rho = (C)p.rho0 + drho;
+    // Untagged kernels have the registers, but for the force's on D3Q27.  256 x 256 x 200
+    // Smagorinsky with a force, us a step, one step a pass / kept / formed anew: D3Q27 periodic
+    // FP32 525 / 1015 / 356, FP64 1026 / 1528 / 692, cavity FP32 560 / 1240 / 462; D3Q19 cavity
+    // FP32 384 / 432 / 310
+    auto par = [&](double v) { return node_param<TWO && (TAGGED || (FORCE && Q == 27))>(v, h[0]); };
+    const C Fx = FORCE ? par(p.force[0]) : C(0), Fy = FORCE ? par(p.force[1]) : C(0), Fz = FORCE ? par(p.force[2]) : C(0);
+    const C rho = par(p.rho0) + drho;
     C inv_rho = C(1) / rho;
     if constexpr (FORCE) {
         px = fm(C(0.5), Fx, px);
@@ -426,9 +441,9 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
     auto ev_of = [&](auto K, C cu) {
         return C(V<Q, decltype(K)::value>::w) * fm(rho, fm(cu, C(4.5) * cu, uu15), drho);
     };
-    C wp = (C)p.omega, wm = (C)p.omega;
+    C wp = par(p.omega), wm = wp;
     if constexpr ((MS & MS_TRT) != 0) {
-        if (tag == LBM_TAG_TRT) wm = (C)p.omega_minus;
+        if (tag == LBM_TAG_TRT) wm = par(p.omega_minus);
     }
     if constexpr ((MS & MS_SMAG) != 0) {
         C pxx = C(0), pyy = C(0), pzz = C(0), pxy = C(0), pxz = C(0), pyz = C(0);
@@ -445,8 +460,8 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
             if constexpr (Vk::y * Vk::z != 0) pyz += C(Vk::y * Vk::z) * ne;
         });
         const C qn = sqrt(fm(C(2), fm(pyz, pyz, fm(pxy, pxy, pxz * pxz)), fm(pzz, pzz, fm(pxx, pxx, pyy * pyy))));
-        const C tau0 = (C)p.tau;
-        const C tau_s = C(0.5) * (tau0 + sqrt(fm(tau0, tau0, (qn * (C)p.smag_c) * inv_rho)));
+        const C tau0 = par(p.tau);
+        const C tau_s = C(0.5) * (tau0 + sqrt(fm(tau0, tau0, (qn * par(p.smag_c)) * inv_rho)));
         if (tag == LBM_TAG_BGK_SMAG) {
             wp = C(1) / tau_s;
             wm = wp;
@@ -454,7 +469,7 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
     }
     // in the two-step kernel, whose registers are short: form the equilibria again
     // rather than keep them from the momentum flux
-    if constexpr (!FORCE && (MS & MS_SMAG) != 0) asm("" : "+v"(inv_rho), "+v"(uu15));
+    if constexpr (TWO && (TAGGED || !FORCE || Q == 27) && (MS & MS_SMAG) != 0) asm("" : "+v"(inv_rho), "+v"(uu15));
     hs[0] = fm(-fm(C(-V<Q, 0>::w), fm(C(-1.5) * rho, uu, drho), h[0]), wp, h[0]);
     // rounded to FP32 before it is to FP16, as where the force's term follows
     if constexpr (!FORCE) asm("" : "+v"(hs[0]));
@@ -508,7 +523,7 @@ __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live
     // collide_pairs, and their steps, limited by instruction issue, are up to 11% faster
     // with it (101^3 D3Q27 TRT 23.0 against 25.8 us)
     if constexpr ((P != 2 || TWO) && (MS == MS_BGK || MS == MS_TRT || MS == (MS_BGK | MS_SMAG))) {
-        collide_pairs<Q, C, MS, TAGGED, FORCE>(h, tag, p, hs, P == 2 && even && p.pair);
+        collide_pairs<Q, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, P == 2 && even && p.pair);
         return;
     }
     if constexpr (MS == (MS_BGK | MS_SMAG | MS_MLP)) {
