@@ -191,9 +191,8 @@ size_t lbm_population_bytes(const lbm_config *cfg);
  * mostly fluid (rows of the default launch shape, models BGK, TRT, BGK +
  * Smagorinsky, regularized, recursive), a second array of the populations' size
  * where that is at most 1/8 of the free device memory: four or more steps in
- * one call then go through it two at a time (same populations, bitwise up to
- * where the compiler fuses a multiply-add differently in the regularized models).
- * The slots of non-fluid nodes hold unspecified values: a step may overwrite them.
+ * one call then go through it two at a time (the same populations, bit for bit:
+ * neither how calls group the steps nor the free memory matters).  The slots of non-fluid nodes hold unspecified values: a step may overwrite them.
  * Errors: EINVAL (config or tags), ENOMEM, EHIP. */
 lbm_status lbm_create(const lbm_config *cfg, const uint8_t *tags_host, void *hip_stream,
                       lbm_lattice **out);

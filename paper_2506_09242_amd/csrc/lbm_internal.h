@@ -141,10 +141,10 @@ constexpr int two_max_tx(int prec) { return prec == LBM_F64 ? 64 : 128; }
 // Lattices it is built for.  In FP16 two updates of a node cost more than the pass
 // they save where the update is long: 256 x 256 x 200, us a step, in place / two in one
 // pass: D3Q27 BGK 274 / 221, Smagorinsky 269 / 258, with a body force 274 / 323; D3Q19 BGK
-// 182 / 160, with a force on 250 x 243 x 230 221 / 226, Smagorinsky 185 / 191, recursive
-// 187 / 203.  Walled FP16 lattices are never faster (the cost in plan_two).
+// 182 / 160, with a force on 250 x 243 x 230 221 / 226, Smagorinsky 185 / 191; recursive D3Q27
+// 282 / 255, D3Q19 186 / 183.  Walled FP16 lattices are never faster (the cost in plan_two).
 constexpr bool two_built(int q, int prec, int ms, bool tagged, bool force) {
-    if (prec == LBM_F16S && (tagged || force || ms == MS_RR || (q == 19 && ms == (MS_BGK | MS_SMAG)))) return false;
+    if (prec == LBM_F16S && (tagged || force || (q == 19 && (ms == MS_RR || ms == (MS_BGK | MS_SMAG))))) return false;
     return ms == MS_BGK || ms == MS_TRT || ms == MS_REG || ms == MS_RR || ms == (MS_BGK | MS_SMAG);
 }
 // Two steps of the whole lattice from p.pops into dst, layout parity unchanged.

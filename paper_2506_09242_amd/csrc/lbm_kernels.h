@@ -172,6 +172,16 @@ __device__ __forceinline__ void open_boundary(const C (&h)[Q], int tag, const St
     });
 }
 
+// A kernel parameter as the two-step kernel uses it.  FRESH ties it to a value of the
+// node, so that what is computed from parameters alone (weights times forces and
+// rates) is formed for each node and not kept in registers across the march over
+// planes: there it is spilled, and its reload waits for the populations in flight.
+template <bool FRESH, typename C>
+__device__ __forceinline__ C node_param(double v, C h) {
+    if constexpr (FRESH) asm("" : "+s"(v) : "v"(h));
+    return (C)v;
+}
+
 // Collision of one node in shifted form (pair split, Guo forcing).  Every lane
 // of the wave must call it (the learned closure is evaluated wave-wide).
 // Regularized and recursive-regularized update for lattices whose fluid nodes
@@ -187,10 +197,20 @@ __device__ __forceinline__ void open_boundary(const C (&h)[Q], int tag, const St
 // general path with omega = 1 in its relaxation, where h cancels; only the
 // rounding differs.  Keeping no population live across the update frees the
 // registers the general path needs.
-template <int Q, typename C, int MS>
-__device__ __forceinline__ void collide_regularized(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q]) {
+// Every product-sum is an explicit fused multiply-add and nothing else is fused, so
+// the rounding does not depend on the kernel around it: steps in place and two at a
+// time agree bit for bit.  The forms are those that FP64 and FP16 lattices always had,
+// among them: untagged D3Q19 lattices add u.u, u.F and the cross terms of u and F from x
+// on, all others from y on, and so do the even steps of FP16 lattices with two nodes a
+// lane (pair), which fuse the odd equilibrium and not the force's term.  FORCE: as in
+// collide_pairs.
+template <int Q, typename C, int MS, bool TAGGED, bool FORCE, bool TWO>
+__device__ __forceinline__ void collide_regularized(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q],
+                                                    bool pair) {
+#pragma clang fp contract(off)
     constexpr int H = (Q - 1) / 2;
     constexpr bool RR = MS == MS_RR;
+    auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
     C drho = C(0), jx = C(0), jy = C(0), jz = C(0);
     C sxx = C(0), syy = C(0), szz = C(0), sxy = C(0), sxz = C(0), syz = C(0);
     sfor<Q>([&](auto I) {
@@ -213,86 +233,119 @@ __device__ __forceinline__ void collide_regularized(const C (&h)[Q], int tag, co
         if constexpr (Vi::y * Vi::z == 1) syz += h[i];
         if constexpr (Vi::y * Vi::z == -1) syz -= h[i];
     });
-    const C Fx = (C)p.force[0], Fy = (C)p.force[1], Fz = (C)p.force[2];
-    const C rho = (C)p.rho0 + drho;
+    // (parameters formed anew where their products would spill: as in collide_pairs)
+    auto par = [&](double v) { return node_param<TWO && (TAGGED || (FORCE && Q == 27))>(v, h[0]); };
+    const C Fx = FORCE ? par(p.force[0]) : C(0), Fy = FORCE ? par(p.force[1]) : C(0), Fz = FORCE ? par(p.force[2]) : C(0);
+    const C rho = par(p.rho0) + drho;
     const C inv_rho = C(1) / rho;
-    const C ux = (jx + C(0.5) * Fx) * inv_rho;
-    const C uy = (jy + C(0.5) * Fy) * inv_rho;
-    const C uz = (jz + C(0.5) * Fz) * inv_rho;
-    const C uu = ux * ux + uy * uy + uz * uz;
-    const C uF = ux * Fx + uy * Fy + uz * Fz;
-    const C d3 = drho * C(1.0 / 3.0);
+    C px = jx, py = jy, pz = jz;
+    if constexpr (FORCE) px = fm(C(0.5), Fx, jx), py = fm(C(0.5), Fy, jy), pz = fm(C(0.5), Fz, jz);
+    const C ux = px * inv_rho, uy = py * inv_rho, uz = pz * inv_rho;
+    const bool from_x = Q == 19 && !TAGGED && !pair;
+    const C uu = fm(uz, uz, from_x ? fm(uy, uy, ux * ux) : fm(ux, ux, uy * uy));
+    C uF = C(0);
+    if constexpr (FORCE) uF = fm(uz, Fz, from_x ? fm(uy, Fy, ux * Fx) : fm(ux, Fx, uy * Fy));
+    auto cross = [&](C ua, C Fb, C ub, C Fa, bool from_a) {
+#pragma clang fp contract(off)
+        return from_a ? fm(ub, Fa, ua * Fb) : fm(ua, Fb, ub * Fa);
+    };
+    const C third = C(1.0 / 3.0);
     // Pi1 = Pi + (uF + Fu) / 2
-    const C rxx = sxx - d3 - rho * ux * ux + ux * Fx;
-    const C ryy = syy - d3 - rho * uy * uy + uy * Fy;
-    const C rzz = szz - d3 - rho * uz * uz + uz * Fz;
-    const C rxy = sxy - rho * ux * uy + C(0.5) * (ux * Fy + uy * Fx);
-    const C rxz = sxz - rho * ux * uz + C(0.5) * (ux * Fz + uz * Fx);
-    const C ryz = syz - rho * uy * uz + C(0.5) * (uy * Fz + uz * Fy);
-    const C rtr = (rxx + ryy + rzz) * C(1.0 / 3.0);
+    const C jux = rho * ux, juy = rho * uy, juz = rho * uz;
+    C rxx = fm(-jux, ux, fm(-drho, third, sxx)), ryy = fm(-juy, uy, fm(-drho, third, syy));
+    C rzz = fm(-juz, uz, fm(-drho, third, szz));
+    C rxy = fm(-jux, uy, sxy), rxz = fm(-jux, uz, sxz), ryz = fm(-juy, uz, syz);
+    if constexpr (FORCE) {
+        rxx = fm(ux, Fx, rxx);
+        ryy = fm(uy, Fy, ryy);
+        rzz = fm(uz, Fz, rzz);
+        rxy = fm(C(0.5), cross(ux, Fy, uy, Fx, from_x), rxy);
+        rxz = fm(C(0.5), cross(ux, Fz, uz, Fx, from_x), rxz);
+        ryz = fm(C(0.5), cross(uy, Fz, uz, Fy, from_x && !RR), ryz);
+    }
+    const C rsum = (rxx + ryy) + rzz;
+    const C rtr = rsum * third;
     const bool on = tag == (RR ? LBM_TAG_RR : LBM_TAG_REG);
-    const C om1 = C(1) - (C)p.omega;
+    const C om1 = C(1) - par(p.omega);
     const C reg = on ? om1 * C(4.5) : C(0);
+    // third-order coefficients, each the product of t and its norm
     C t1p = C(0), t1m = C(0), t2p = C(0), t2m = C(0), t3p = C(0), t3m = C(0), t7 = C(0);
+    constexpr double np_ = Q == 19 ? 27.0 / 2.0 : 27.0 / 4.0;  // 1 / norm of a sum
+    constexpr double nm_ = Q == 19 ? 27.0 / 6.0 : 27.0 / 4.0;  // 1 / norm of a difference
     if constexpr (RR) {
         // A2 = (1 - omega) dev Pi1, A3 recursive, T = rho u u u + A3
-        const C axx = om1 * (rxx - rtr), ayy = om1 * (ryy - rtr), azz = om1 * (rzz - rtr);
+        const C axx = om1 * fm(-rsum, third, rxx), ayy = om1 * fm(-rsum, third, ryy), azz = om1 * fm(-rsum, third, rzz);
         const C axy = om1 * rxy, axz = om1 * rxz, ayz = om1 * ryz;
-        const C txxy = rho * ux * ux * uy + C(2) * ux * axy + uy * axx;
-        const C tyzz = rho * uy * uz * uz + uy * azz + C(2) * uz * ayz;
-        const C txzz = rho * ux * uz * uz + ux * azz + C(2) * uz * axz;
-        const C txyy = rho * ux * uy * uy + ux * ayy + C(2) * uy * axy;
-        const C tyyz = rho * uy * uy * uz + C(2) * uy * ayz + uz * ayy;
-        const C txxz = rho * ux * ux * uz + C(2) * ux * axz + uz * axx;
-        constexpr double np_ = Q == 19 ? 27.0 / 2.0 : 27.0 / 4.0;  // 1 / norm of a sum
-        constexpr double nm_ = Q == 19 ? 27.0 / 6.0 : 27.0 / 4.0;  // 1 / norm of a difference
+        const C x2 = ux + ux, y2 = uy + uy, z2 = uz + uz;
+        const C juxy = jux * uy;
+        const C txxy = fm(uy, axx, fm(jux * ux, uy, x2 * axy));
+        const C tyzz = fm(z2, ayz, fm(juy * uz, uz, uy * azz));
+        const C txzz = fm(z2, axz, fm(jux * uz, uz, ux * azz));
+        const C txyy = fm(y2, axy, fm(juxy, uy, ux * ayy));
+        const C tyyz = fm(uz, ayy, fm(juy * uy, uz, y2 * ayz));
+        const C txxz = fm(uz, axx, fm(jux * ux, uz, x2 * axz));
         const C g = on ? C(1) : C(0);
-        t1p = g * (txxy + tyzz) * C(np_);
-        t1m = g * (txxy - tyzz) * C(nm_);
-        t2p = g * (txzz + txyy) * C(np_);
-        t2m = g * (txzz - txyy) * C(nm_);
-        t3p = g * (tyyz + txxz) * C(np_);
-        t3m = g * (tyyz - txxz) * C(nm_);
-        if constexpr (Q == 27) t7 = g * (rho * ux * uy * uz + ux * ayz + uy * axz + uz * axy) * C(27.0);
+        t1p = g * (txxy + tyzz);
+        t1m = g * (txxy - tyzz);
+        t2p = g * (txzz + txyy);
+        t2m = g * (txzz - txyy);
+        t3p = g * (tyyz + txxz);
+        t3m = g * (tyyz - txxz);
+        if constexpr (Q == 27) t7 = g * fm(uz, axy, fm(uy, axz, fm(juxy, uz, ux * ayz)));
     }
 
     // rest population: regularized keeps the trace term, recursive relaxes it with 1
-    hs[0] = C(V<Q, 0>::w) * (drho - C(1.5) * rho * uu - C(1.5) * uF);
-    if constexpr (!RR) hs[0] -= reg * C(V<Q, 0>::w) * rtr;
+    C r0 = fm(C(-1.5) * rho, uu, drho);
+    if constexpr (FORCE) r0 = fm(C(-1.5), uF, r0);
+    if constexpr (RR) hs[0] = C(V<Q, 0>::w) * r0;
+    else hs[0] = fm(C(V<Q, 0>::w), r0, -((reg * C(V<Q, 0>::w)) * rtr));
     sfor<H>([&](auto K) {
+#pragma clang fp contract(off)
         constexpr int k = decltype(K)::value + 1;
         using Vk = V<Q, k>;
         C cu = C(0), cF = C(0), cpc = C(0);
-        if constexpr (Vk::x != 0) cu += C(Vk::x) * ux, cF += C(Vk::x) * Fx, cpc += rxx;
-        if constexpr (Vk::y != 0) cu += C(Vk::y) * uy, cF += C(Vk::y) * Fy, cpc += ryy;
-        if constexpr (Vk::z != 0) cu += C(Vk::z) * uz, cF += C(Vk::z) * Fz, cpc += rzz;
-        if constexpr (Vk::x * Vk::y != 0) cpc += C(2 * Vk::x * Vk::y) * rxy;
-        if constexpr (Vk::x * Vk::z != 0) cpc += C(2 * Vk::x * Vk::z) * rxz;
-        if constexpr (Vk::y * Vk::z != 0) cpc += C(2 * Vk::y * Vk::z) * ryz;
-        const C ev = C(Vk::w) * (drho + rho * (C(4.5) * cu * cu - C(1.5) * uu));
-        const C od = C(Vk::w) * C(3) * rho * cu;
-        const C Fe = C(Vk::w) * (C(9) * cu * cF - C(3) * uF);
-        const C Fo = C(Vk::w) * C(3) * cF;
+        if constexpr (Vk::x != 0) cu = C(Vk::x) * ux, cF += C(Vk::x) * Fx, cpc += rxx;
+        if constexpr (Vk::y != 0) {
+            cu = Vk::x == 0 ? C(Vk::y) * uy : fm(C(Vk::y) * py, inv_rho, cu);
+            cF += C(Vk::y) * Fy, cpc += ryy;
+        }
+        if constexpr (Vk::z != 0) {
+            cu = Vk::x == 0 && Vk::y == 0 ? C(Vk::z) * uz : fm(C(Vk::z) * pz, inv_rho, cu);
+            cF += C(Vk::z) * Fz, cpc += rzz;
+        }
+        if constexpr (Vk::x * Vk::y != 0) cpc = fm(C(2 * Vk::x * Vk::y), rxy, cpc);
+        if constexpr (Vk::x * Vk::z != 0) cpc = fm(C(2 * Vk::x * Vk::z), rxz, cpc);
+        if constexpr (Vk::y * Vk::z != 0) cpc = fm(C(2 * Vk::y * Vk::z), ryz, cpc);
+        C ev = C(Vk::w) * fm(rho, fm(cu, C(4.5) * cu, C(-1.5) * uu), drho);
+        C B = ((C(Vk::w) * C(3)) * rho) * cu;
+        if constexpr (FORCE) {
+            ev = fm(C(0.5), C(Vk::w) * fm(cF, C(9) * cu, C(-3) * uF), ev);
+            const C Fo = (C(Vk::w) * C(3)) * cF;
+            B = pair ? fm((C(Vk::w) * C(3)) * rho, cu, C(0.5) * Fo) : fm(C(0.5), Fo, B);
+        }
         // regularized: |c|^2 -> 1 (tr Q = 0 projection); recursive: |c|^2 (deviatoric)
-        const C R = reg * C(Vk::w) * (cpc - rtr * C(RR ? Vk::n2 : 1));
-        C E = C(0);
+        constexpr int nt = RR ? Vk::n2 : 1;
+        const C dev = nt == 1 ? fm(-rsum, third, cpc) : fm(-rtr, C(nt), cpc);
+        const C A = fm(reg * C(Vk::w), dev, ev);
         if constexpr (RR) {
             constexpr int cx = Vk::x, cy = Vk::y, cz = Vk::z;
-            constexpr double p1p = cy * (cx * cx + cz * cz - 2.0 / 3.0), p1m = cy * (cx * cx - cz * cz);
-            constexpr double p2p = cx * (cy * cy + cz * cz - 2.0 / 3.0), p2m = cx * (cz * cz - cy * cy);
-            constexpr double p3p = cz * (cx * cx + cy * cy - 2.0 / 3.0), p3m = cz * (cy * cy - cx * cx);
-            constexpr double p7 = cx * cy * cz;
-            if constexpr (p1p != 0.0) E += C(p1p) * t1p;
-            if constexpr (p1m != 0.0) E += C(p1m) * t1m;
-            if constexpr (p2p != 0.0) E += C(p2p) * t2p;
-            if constexpr (p2m != 0.0) E += C(p2m) * t2m;
-            if constexpr (p3p != 0.0) E += C(p3p) * t3p;
-            if constexpr (p3m != 0.0) E += C(p3m) * t3m;
-            if constexpr (Q == 27 && p7 != 0.0) E += C(p7) * t7;
-            E *= C(Vk::w);
+            C E = C(0);
+            // E += p norm t, p a polynomial of c_k: of its two products the one with p is fused,
+            // or, where p is 1 or -1, the one with the norm
+            auto add = [&](double p, double norm, C t) {
+#pragma clang fp contract(off)
+                if (p == 1.0 || p == -1.0) E = fm(C(p) * t, C(norm), E);
+                else if (p != 0.0) E = fm(C(p), t * C(norm), E);
+            };
+            add(cy * (cx * cx + cz * cz - 2.0 / 3.0), np_, t1p);
+            add(cy * (cx * cx - cz * cz), nm_, t1m);
+            add(cx * (cy * cy + cz * cz - 2.0 / 3.0), np_, t2p);
+            add(cx * (cz * cz - cy * cy), nm_, t2m);
+            add(cz * (cx * cx + cy * cy - 2.0 / 3.0), np_, t3p);
+            add(cz * (cy * cy - cx * cx), nm_, t3m);
+            if constexpr (Q == 27) add(cx * cy * cz, 27.0, t7);
+            B = fm(E, C(Vk::w), B);
         }
-        const C A = ev + C(0.5) * Fe + R;
-        const C B = od + C(0.5) * Fo + E;
         hs[k] = A + B;
         hs[k + H] = A - B;
     });
@@ -375,16 +428,6 @@ __device__ __forceinline__ void collide_closure(const C (&h)[Q], int tag, bool l
     });
 }
 
-// A kernel parameter as the two-step kernel uses it.  FRESH ties it to a value of the
-// node, so that what is computed from parameters alone (weights times forces and
-// rates) is formed for each node and not kept in registers across the march over
-// planes: there it is spilled, and its reload waits for the populations in flight.
-template <bool FRESH, typename C>
-__device__ __forceinline__ C node_param(double v, C h) {
-    if constexpr (FRESH) asm("" : "+s"(v) : "v"(h));
-    return (C)v;
-}
-
 // BGK, BGK + Smagorinsky and two-relaxation-time updates for lattices whose fluid
 // nodes use only these, pair by pair: h* = h - omega+ (even part of h - heq) -+
 // omega- (odd part), plus the Guo terms.  The same sums and products, in the same
@@ -395,9 +438,9 @@ __device__ __forceinline__ C node_param(double v, C h) {
 // exactly zero, so both forms give the same result.  TAGGED: untagged D3Q19 BGK and
 // TRT lattices add u.u and u.F from x on, all others from y on (the order their
 // kernels always had), and so do the even steps of FP16 lattices with two nodes a
-// lane (from_y).
+// lane (pair).
 template <int Q, typename C, int MS, bool TAGGED, bool FORCE, bool TWO>
-__device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q], bool from_y) {
+__device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const StepParams &p, C (&hs)[Q], bool pair) {
     constexpr int H = (Q - 1) / 2;
     auto fm = [](C a, C b, C c) { return __builtin_elementwise_fma(a, b, c); };
     C drho = C(0), px = C(0), py = C(0), pz = C(0);
@@ -427,7 +470,7 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
     }
     const C ux = px * inv_rho, uy = py * inv_rho, uz = pz * inv_rho;
     constexpr bool kFromX = Q == 19 && !TAGGED && (MS == MS_BGK || MS == MS_TRT);
-    const C uu = fm(uz, uz, kFromX && !from_y ? fm(uy, uy, ux * ux) : fm(ux, ux, uy * uy));
+    const C uu = fm(uz, uz, kFromX && !pair ? fm(uy, uy, ux * ux) : fm(ux, ux, uy * uy));
     C uu15 = C(-1.5) * uu;
     // c.u and the even part of the equilibrium of pair k
     auto cu_of = [&](auto K) {
@@ -506,24 +549,25 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
 
 // Regularized / recursive-regularized lattices take the moment-only update
 // (collide_regularized).
-// P: storage precision; TWO: in the two-step kernel (even: the update of an even step).
+// P: storage precision; TWO: in the two-step kernel; pair: with the rounding of the even
+// step with two nodes a lane.
 template <int Q, int P, typename C, int MS, bool TAGGED, bool FORCE = true, bool TWO = false>
 __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live, const StepParams &p, C (&hs)[Q],
-                                             bool even = false) {
+                                             bool pair = false) {
     if constexpr (MS == MS_STREAM) {
         // collision switched off: the step only streams (and bounces back)
         sfor<Q>([&](auto I) { hs[decltype(I)::value] = h[decltype(I)::value]; });
         return;
     }
     if constexpr (MS == MS_REG || MS == MS_RR) {
-        collide_regularized<Q, C, MS>(h, tag, p, hs);
+        collide_regularized<Q, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, pair);
         return;
     }
     // FP16 lattices a step at a time keep the general update below: the same bits as
     // collide_pairs, and their steps, limited by instruction issue, are up to 11% faster
     // with it (101^3 D3Q27 TRT 23.0 against 25.8 us)
     if constexpr ((P != 2 || TWO) && (MS == MS_BGK || MS == MS_TRT || MS == (MS_BGK | MS_SMAG))) {
-        collide_pairs<Q, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, P == 2 && even && p.pair);
+        collide_pairs<Q, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, pair);
         return;
     }
     if constexpr (MS == (MS_BGK | MS_SMAG | MS_MLP)) {
@@ -1169,7 +1213,7 @@ __global__ __launch_bounds__(256) void k_collide_pair_even(StepParams p) {
             constexpr int i = decltype(I)::value;
             h[i] = k == 0 ? half_lo(u[i]) : half_hi(u[i]);
         });
-        collide_node<Q, 2, C, MS, false>(h, tag, true, p, hs);
+        collide_node<Q, 2, C, MS, false>(h, tag, true, p, hs, true);
         sfor<Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (k == 0) o[i] = half_bits(hs[i]);

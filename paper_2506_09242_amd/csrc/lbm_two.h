@@ -235,7 +235,7 @@ __global__ __launch_bounds__(two_region(P) / 64 * 64 + 64) void k_two_steps(Step
         {
             C h[Q];
             sfor<Q>([&](auto I) { h[decltype(I)::value] = live ? (C)v[decltype(I)::value] : C(0); });
-            collide_node<Q, P, C, MS, TAGGED, FORCE, true>(h, tag_of(m_cur), live, p, hs, PARITY == 0);
+            collide_node<Q, P, C, MS, TAGGED, FORCE, true>(h, tag_of(m_cur), live, p, hs, P == 2 && PARITY == 0 && p.pair);
             if constexpr (TAGGED) wall_term(m_cur, ze, hs);
         }
         g[0] = rest;
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(two_region(P) / 64 * 64 + 64) void k_two_steps(Step
             if constexpr (RING3) gather_part(std::false_type{});
             gather_part(std::true_type{});
             C gs[Q];
-            collide_node<Q, P, C, MS, TAGGED, FORCE, true>(g, tag_of(m_own), on, p, gs, PARITY == 1);
+            collide_node<Q, P, C, MS, TAGGED, FORCE, true>(g, tag_of(m_own), on, p, gs, P == 2 && PARITY == 1 && p.pair);
             if constexpr (TAGGED) wall_term(m_own, zo, gs);
             const unsigned own = lane_off(zo, yb[1], xb[1]);
             const int zv[3] = {wrapz(zo - 1), zo, wrapz(zo + 1)};
@@ -330,12 +330,12 @@ static hipError_t launch_two_par(const StepParams &p, void *dst, const TwoTiles 
     return hipGetLastError();
 }
 
-// Without a body force the Guo terms are left out (collide_pairs): fewer registers.
+// Without a body force the Guo terms are left out (collide_pairs, collide_regularized):
+// fewer registers.
 template <int Q, int P, int MS, bool TG>
 static hipError_t launch_two_force(const StepParams &p, void *dst, const TwoTiles &w, int parity, hipStream_t s) {
-    constexpr bool kPairs = MS != MS_RR && MS != MS_REG;
     if constexpr (two_built(Q, P, MS, TG, false)) {
-        if (!p.has_force) return launch_two_par<Q, P, MS, TG, !kPairs>(p, dst, w, parity, s);
+        if (!p.has_force) return launch_two_par<Q, P, MS, TG, false>(p, dst, w, parity, s);
     }
     if constexpr (two_built(Q, P, MS, TG, true)) {
         if (p.has_force) return launch_two_par<Q, P, MS, TG, true>(p, dst, w, parity, s);

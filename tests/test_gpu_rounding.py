@@ -22,8 +22,8 @@ FORCE = (1e-4, -2e-4, 5e-5)
 WALLS = [(0.1, 0.02, 0.0), (0.0, -0.05, 0.03)]
 
 
-def digest(module, q, prec, model, geom, force):
-    nx, ny, nz = 33, 18, 14
+def digest(module, q, prec, model, geom, force, shape=(33, 18, 14)):
+    nx, ny, nz = shape
     tag = MODELS[model]
     tags = inputs.all_fluid(nx, ny, nz, tag) if geom == "periodic" else \
         inputs.random_tags(nx, ny, nz, 5, 0.15, 0.05, (tag,))
@@ -34,6 +34,15 @@ def digest(module, q, prec, model, geom, force):
     h = L.read_state() + 0.0  # one zero
     L.close()
     return hashlib.sha256(np.ascontiguousarray(h).tobytes()).hexdigest()[:16]
+
+
+@pytest.mark.parametrize("q", [19, 27])
+def test_two_nodes_a_lane_are_bitwise_what_they_were(q):
+    """FP16 rows of 128 nodes: row-form addresses, even steps with two nodes a lane."""
+    lines = [l.split() for l in open(GOLDEN.replace("digests", "digests_rows")) if not l.startswith("#")]
+    mine = [l for l in lines if l[0] == str(q)]
+    assert len(mine) == 20
+    assert [l for l in mine if digest(lbm, q, "f16s", *l[2:5], shape=(128, 9, 11)) != l[5]] == []
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
