@@ -584,10 +584,11 @@ __device__ __forceinline__ void collide_node(const C (&h)[Q], int tag, bool live
         collide_regularized<Q, P, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, pair);
         return;
     }
-    // FP16 lattices a step at a time keep the general update below: the same bits as
-    // collide_pairs, and their steps, limited by instruction issue, are up to 11% faster
-    // with it (101^3 D3Q27 TRT 23.0 against 25.8 us)
-    if constexpr ((P != 2 || TWO) && (MS == MS_BGK || MS == MS_TRT || MS == (MS_BGK | MS_SMAG))) {
+    // FP32 and FP16 lattices a step at a time keep the general update below: the same bits
+    // as collide_pairs, and the compiler's own order is the faster one there (us a step, this
+    // / collide_pairs: 64^3 D3Q19 FP32 TRT cavity 9.9 / 10.5, 101^3 D3Q27 FP32 TRT with a force
+    // 34.7 / 36.3, FP16 TRT 23.0 / 25.8); in FP64 the slower one (101^3 D3Q19 BGK cavity 1.09)
+    if constexpr ((P == 0 || TWO) && (MS == MS_BGK || MS == MS_TRT || MS == (MS_BGK | MS_SMAG))) {
         collide_pairs<Q, C, MS, TAGGED, FORCE, TWO>(h, tag, p, hs, pair);
         return;
     }
