@@ -1370,9 +1370,11 @@ __device__ __forceinline__ void node_fields(const AuxParams &a, const double (&f
     u[2] = (jz + 0.5 * a.force[2]) * inv;
 }
 
-// Box filter: a block takes 256 / factor coarse nodes of one coarse row, a thread
-// one fine column of x (every 256th beyond a factor of 256), whose factor^2 nodes it
-// sums; the columns of a coarse node are then added through LDS.  Bound by memory:
+// Box filter: a block takes 256 / factor consecutive coarse nodes, a thread one fine
+// column of x (every 256th beyond a factor of 256), whose factor^2 nodes it sums; the
+// columns of a coarse node are then added through LDS.  Coarse rows do not end a block:
+// short ones (64 nodes, factor 8: eight coarse nodes of 32) would leave it mostly idle, and
+// one block a row is more than a launch takes on flat lattices.  Bound by memory:
 // one read of the populations, where a gather of the fields to FP64 planes and a
 // filter of those moved them to memory and back (256^3 D3Q27 FP32, factor 4, the
 // whole call: 15.1 ms with those and their 580 MB allocated and freed, 0.35 ms now).
@@ -1380,13 +1382,12 @@ template <int Q, int P>
 __global__ __launch_bounds__(256) void k_filter(AuxParams a, int factor, int cx, int cy, int cz, double *coarse) {
     __shared__ double s[kCoarsePlanes][256];
     const int cols = factor < 256 ? factor : 256, per = 256 / cols;  // columns of a coarse node, coarse nodes a block
-    const int segs = (cx + per - 1) / per;
-    const int seg = blockIdx.x % segs, row = blockIdx.x / segs;
-    const int Y = row % cy, Z = row / cy;
+    const unsigned nc = (unsigned)cx * cy * cz, first = blockIdx.x * (unsigned)per;
     const int t = threadIdx.x, c = t / cols, xi = t - c * cols;
-    const int X = seg * per + c;
+    const unsigned n = first + c, row = n / (unsigned)cx;  // of this thread's columns
+    const int X = (int)(n - row * cx), Z = (int)(row / (unsigned)cy), Y = (int)(row - (unsigned)Z * cy);
     double v[kCoarsePlanes] = {};
-    if (c < per && X < cx) {
+    if (c < per && n < nc) {
         for (int dz = 0; dz < factor; ++dz)
             for (int dy = 0; dy < factor; ++dy)
                 for (int dx = xi; dx < factor; dx += cols) {
@@ -1411,28 +1412,27 @@ __global__ __launch_bounds__(256) void k_filter(AuxParams a, int factor, int cx,
     for (int k = 0; k < kCoarsePlanes; ++k) s[k][t] = v[k];
     __syncthreads();
     for (int q = t; q < per * kCoarsePlanes; q += 256) {
-        const int k = q / per, n = q - k * per;
+        const int k = q / per, e = (q - k * per) * cols;
         double sum = 0.0;
-        for (int j = 0; j < cols; ++j) sum += s[k][n * cols + j];
-        s[k][n * cols] = sum;
+        for (int j = 0; j < cols; ++j) sum += s[k][e + j];
+        s[k][e] = sum;
     }
     __syncthreads();
-    const int Xo = seg * per + t;
-    if (t >= per || Xo >= cx) return;
+    const long long o = first + (unsigned)t;
+    if (t >= per || o >= nc) return;
     const int e = t * cols;
-    const long long nc = (long long)cx * cy * cz, o = ((long long)Z * cy + Y) * cx + Xo;
     const double vol = (double)factor * factor * factor, sr = s[0][e];
     const double Ux = s[1][e] / sr, Uy = s[2][e] / sr, Uz = s[3][e] / sr;
     coarse[o] = sr / vol;
     coarse[nc + o] = Ux;
-    coarse[2 * nc + o] = Uy;
-    coarse[3 * nc + o] = Uz;
-    coarse[4 * nc + o] = s[4][e] / sr - Ux * Ux;
-    coarse[5 * nc + o] = s[5][e] / sr - Uy * Uy;
-    coarse[6 * nc + o] = s[6][e] / sr - Uz * Uz;
-    coarse[7 * nc + o] = s[7][e] / sr - Ux * Uy;
-    coarse[8 * nc + o] = s[8][e] / sr - Ux * Uz;
-    coarse[9 * nc + o] = s[9][e] / sr - Uy * Uz;
+    coarse[2ll * nc + o] = Uy;
+    coarse[3ll * nc + o] = Uz;
+    coarse[4ll * nc + o] = s[4][e] / sr - Ux * Ux;
+    coarse[5ll * nc + o] = s[5][e] / sr - Uy * Uy;
+    coarse[6ll * nc + o] = s[6][e] / sr - Uz * Uz;
+    coarse[7ll * nc + o] = s[7][e] / sr - Ux * Uy;
+    coarse[8ll * nc + o] = s[8][e] / sr - Ux * Uz;
+    coarse[9ll * nc + o] = s[9][e] / sr - Uy * Uz;
 }
 
 template <int Q, int P>
@@ -1631,7 +1631,7 @@ template <int Q, int P>
 hipError_t launch_filter(const AuxParams &a, int factor, double *coarse, hipStream_t s) {
     const int cx = a.nx / factor, cy = a.ny / factor, cz = a.nz / factor;
     const int per = 256 / (factor < 256 ? factor : 256);
-    const long long blocks = (long long)((cx + per - 1) / per) * cy * cz;
+    const long long blocks = ((long long)cx * cy * cz + per - 1) / per;
     k_filter<Q, P><<<(unsigned)blocks, 256, 0, s>>>(a, factor, cx, cy, cz, coarse);
     return hipGetLastError();
 }
