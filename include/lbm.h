@@ -282,6 +282,11 @@ lbm_status lbm_reduce(lbm_lattice *lat, lbm_moments *out);
  * 4 doubles per node (the handle's, where it has one that large).  Synchronizes. */
 lbm_status lbm_enstrophy(lbm_lattice *lat, double *out);
 
+/* Time steps per pass over the populations of lbm_step calls of four and more (and
+ * of lbm_step_reduce between samples as far apart): 2 where the handle has a second
+ * array for it (see lbm_create), else 1; -1 for a null handle. */
+int lbm_steps_per_pass(const lbm_lattice *lat);
+
 /* Wait for all work queued on the handle's stream. */
 lbm_status lbm_synchronize(lbm_lattice *lat);
 

@@ -818,6 +818,8 @@ extern "C" lbm_status lbm_set_launch(lbm_lattice *lat, int tx, int ty) {
 
 extern "C" const char *lbm_variant_name(const lbm_lattice *lat) { return lat ? lat->variant : ""; }
 
+extern "C" int lbm_steps_per_pass(const lbm_lattice *lat) { return lat ? (lat->two ? 2 : 1) : -1; }
+
 extern "C" int64_t lbm_time(const lbm_lattice *lat) { return lat ? lat->t : -1; }
 
 extern "C" lbm_status lbm_synchronize(lbm_lattice *lat) {

@@ -66,6 +66,7 @@ SIGNATURES = {
     "lbm_step_reduce": (C.c_int, [_P, C.c_int64, C.c_int64, C.POINTER(LbmMoments), C.c_int64]),
     "lbm_step_reduce_noalloc": (C.c_int, [_P, C.c_int64, C.c_int64, C.POINTER(LbmMoments), C.c_int64]),
     "lbm_reduce": (C.c_int, [_P, C.POINTER(LbmMoments)]),
+    "lbm_steps_per_pass": (C.c_int, [_P]),
     "lbm_synchronize": (C.c_int, [_P]),
     "lbm_enstrophy": (C.c_int, [_P, C.POINTER(C.c_double)]),
     "lbm_time": (C.c_int64, [_P]),
@@ -268,6 +269,10 @@ class Lattice:
     @property
     def time(self) -> int:
         return lib().lbm_time(self.h)
+
+    @property
+    def steps_per_pass(self) -> int:
+        return lib().lbm_steps_per_pass(self.h)
 
     @property
     def stream_handle(self) -> int:

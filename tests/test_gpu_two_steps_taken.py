@@ -1,0 +1,100 @@
+"""The two-step kernel on lattices that take it, which every case asserts: equal to single
+steps, bit for bit, for every model, precision and lattice it is built for, with and
+without walls and a body force; and where it must not be taken.
+"""
+import numpy as np
+import pytest
+
+from paper_2506_09242_amd import inputs, lbm
+
+pytestmark = pytest.mark.gpu
+KW = dict(tau=0.6, smag_cs=0.1, wall_velocity=[(0.1, 0.02, 0.0), (0.0, -0.05, 0.03)])
+MODELS = [lbm.TAG_BGK, lbm.TAG_TRT, lbm.TAG_SMAG, lbm.TAG_REG, lbm.TAG_RR]
+FORCES = [(0.0, 0.0, 0.0), (1e-4, -2e-4, 5e-5)]
+
+
+def _check(tags, q, prec, force, torch_buffer=False):
+    nz, ny, nx = tags.shape
+    out = []
+    for grouped in (False, True):
+        L = lbm.Lattice(tags, q=q, prec=prec, force=force, layout="rows", torch_buffer=torch_buffer, **KW)
+        assert L.steps_per_pass == 2
+        L.init_equilibrium(*inputs.random_fields(nx, ny, nz, seed=4))
+        for n in (5, 10):  # the second run starts at odd layout parity
+            for k in ([n] if grouped else [1] * n):
+                L.step(k)
+            out.append(L.read_state())
+        L.close()
+    assert np.array_equal(out[0], out[2]) and np.array_equal(out[1], out[3])
+    assert np.isfinite(out[1]).all() and np.abs(out[1] - out[0]).max() > 0.0
+
+
+@pytest.mark.parametrize("force", FORCES)
+@pytest.mark.parametrize("tag", MODELS)
+@pytest.mark.parametrize("q", [19, 27])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_periodic(prec, q, tag, force):
+    """Rows that are not whole tiles, planes that are not whole blocks."""
+    _check(inputs.all_fluid(201, 130, 141, tag), q, prec, force)
+
+
+@pytest.mark.parametrize("force", FORCES)
+@pytest.mark.parametrize("tag", MODELS)
+@pytest.mark.parametrize("q", [19, 27])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_walls(prec, q, tag, force):
+    """Random solid and moving-wall nodes, also across the periodic edges."""
+    _check(inputs.random_tags(192, 130, 141, 11, 0.1, 0.05, (tag,)), q, prec, force)
+
+
+@pytest.mark.parametrize("shape", [(256, 160, 160), (250, 254, 130)])
+@pytest.mark.parametrize("q,tag", [(19, lbm.TAG_BGK), (19, lbm.TAG_TRT), (19, lbm.TAG_REG)] + [(27, t) for t in MODELS])
+def test_fp16(shape, q, tag):
+    _check(inputs.all_fluid(*shape, tag), q, "f16s", FORCES[0])
+
+
+def test_caller_buffer():
+    _check(inputs.all_fluid(201, 130, 141, lbm.TAG_BGK), 19, "f32", FORCES[0], torch_buffer=True)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
+def test_full_size_taylor_green(prec):
+    """512^3 D3Q27, 3.6e9 population elements: sampled nodes after nine steps."""
+    n, steps = 512, 9
+    x = np.arange(n) * (2 * np.pi / n)
+    z, y, x = x[:, None, None], x[None, :, None], x[None, None, :]
+    u = np.empty((3, n, n, n))
+    u[0], u[1], u[2] = 0.05 * np.sin(x) * np.cos(y) * np.cos(z), -0.05 * np.cos(x) * np.sin(y) * np.cos(z), 0.013
+    cells = np.unique(np.concatenate([np.arange(0, n ** 3, 1000003), n ** 3 - 1 - np.arange(0, 4096, 7),
+                                      2 ** 31 // 27 + np.arange(-600, 600, 5)]))
+    L = lbm.Lattice(inputs.all_fluid(n, n, n, lbm.TAG_SMAG), q=27, prec=prec, tau=0.508, smag_cs=0.1)
+    assert L.steps_per_pass == 2
+    out = []
+    for calls in ([steps], [1] * steps):
+        L.init_equilibrium(None, u)
+        for k in calls:
+            L.step(k)
+        out.append(L.read_cells(cells))
+    L.close()
+    assert np.array_equal(out[0], out[1])
+    assert np.isfinite(out[0]).all() and out[0].std() > 0.0
+
+
+@pytest.mark.parametrize("tags,kw", [
+    (lambda: inputs.all_fluid(64, 64, 64), dict(prec="f32")),                               # in the cache
+    (lambda: inputs.all_fluid(256, 160, 160), dict(prec="f16s", force=FORCES[1])),
+    (lambda: inputs.random_tags(256, 160, 160, 3, 0.02, 0.0), dict(prec="f16s")),           # walled FP16
+    (lambda: inputs.random_tags(192, 130, 141, 3, 0.3, 0.0), dict(prec="f64")),             # over a quarter solid
+    (lambda: inputs.all_fluid(192, 144, 144), dict(prec="f64", layout="bricks")),
+    (lambda: inputs.all_fluid(192, 130, 141, lbm.TAG_MLP), dict(prec="f64")),
+    (lambda: inputs.all_fluid(192, 130, 141), dict(prec="f64", free_stream=True))])
+def test_where_it_is_not_taken(tags, kw):
+    with lbm.Lattice(tags(), q=19, **kw) as L:
+        assert L.steps_per_pass == 1
+
+
+def test_an_explicit_launch_shape_turns_it_off():
+    with lbm.Lattice(inputs.all_fluid(192, 130, 141), q=19, prec="f64") as L:
+        assert L.steps_per_pass == 2
+        L.set_launch(64, 4)
+        assert L.steps_per_pass == 1
