@@ -190,7 +190,8 @@ size_t lbm_population_bytes(const lbm_config *cfg);
  * than one fluid model, a few per-tile words, and, on larger lattices that are
  * mostly fluid (rows of the default launch shape, models BGK, TRT, BGK +
  * Smagorinsky, regularized, recursive), a second array of the populations' size
- * where that is at most 1/8 of the free device memory: four or more steps in
+ * where that is at most 1/8 of the free device memory and all of the process's
+ * second arrays together at most 1/4 of the device's: four or more steps in
  * one call then go through it two at a time (the same populations, bit for bit:
  * neither how calls group the steps nor the free memory matters).  The slots of non-fluid nodes hold unspecified values: a step may overwrite them.
  * Errors: EINVAL (config or tags), ENOMEM, EHIP. */

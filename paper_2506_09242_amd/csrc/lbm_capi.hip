@@ -260,6 +260,10 @@ bool plan_two(lbm_lattice *L, bool tagged) {
     return two_us < 0.95 * 2.0 * one_us;
 }
 
+// Bytes of second arrays that the lattices of this process hold on each device.
+std::atomic<long long> g_second_bytes[64];
+std::atomic<long long> &second_bytes(int device) { return g_second_bytes[std::min(std::max(device, 0), 63)]; }
+
 StepParams step_params(const lbm_lattice *L) {
     StepParams p{};
     const lbm_config &c = L->cfg;
@@ -652,17 +656,25 @@ static lbm_status create_impl(const lbm_config *cfg, const uint8_t *tags_host, v
         L->own_pops = true;
     }
     // The second array of the two-step kernel: an extra, so only where it takes a
-    // small part of what is free, and without it the lattice steps in place.  Not
+    // small part of what is free and all of them together at most a quarter of the
+    // device (a program that fills the memory with small lattices got half as many of
+    // them before), and without it the lattice steps in place.  Not
     // where over a quarter of the nodes are solid (rows of a 144 x 176 x 112 rock of
     // porosity 0.20: 0.85 times as fast as the one-step kernels, which skip solid waves).
     if (!brick && two_built(cfg->q, cfg->prec, ms, tagged, step_params(L).has_force) && 4 * nf >= 3 * N &&
         plan_two(L, tagged)) {
         size_t free_b = 0, total_b = 0;
-        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need_bytes <= free_b / 8 &&
-            hipMalloc(&L->d_pops2, need_bytes) == hipSuccess)
-            L->two = true;
-        else
-            L->d_pops2 = nullptr;
+        const long long bytes = (long long)need_bytes;
+        std::atomic<long long> &held = second_bytes(L->device);
+        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need_bytes <= free_b / 8) {
+            if (held.fetch_add(bytes) + bytes <= (long long)(total_b / 4) &&
+                hipMalloc(&L->d_pops2, need_bytes) == hipSuccess) {
+                L->two = true;
+            } else {
+                L->d_pops2 = nullptr;
+                held.fetch_sub(bytes);
+            }
+        }
         (void)hipGetLastError();
     }
     e = hipMalloc(&L->d_tags, (size_t)N);
@@ -787,7 +799,10 @@ extern "C" void lbm_destroy(lbm_lattice *lat) {
     if (!lat) return;
     if (lat->stream || lat->d_pops) (void)hipStreamSynchronize(lat->stream);
     if (lat->own_pops && lat->d_pops) (void)hipFree(lat->d_pops);
-    if (lat->d_pops2) (void)hipFree(lat->d_pops2);
+    if (lat->d_pops2) {
+        (void)hipFree(lat->d_pops2);
+        second_bytes(lat->device).fetch_sub((long long)((size_t)lat->n_elems * elem_bytes(lat->cfg.prec)));
+    }
     if (lat->d_scratch) (void)hipFree(lat->d_scratch);
     if (lat->h_staging) (void)hipHostFree(lat->h_staging);
     if (lat->d_tags) (void)hipFree(lat->d_tags);
