@@ -209,15 +209,21 @@ int default_txl(int nx) {
     return best;
 }
 
-// Tiling of the two-step kernel, and whether it pays.  A block marches alone on
-// its CU (LDS), so a launch takes ceil(blocks / CUs) rounds of (chunk + 2) planes;
+// Tiling of the two-step kernel, and whether it pays.  One block of FP32 and FP64
+// lattices fills a CU (LDS; FP16 ones are planned the same), so a launch takes
+// ceil(blocks / CUs) rounds of (chunk + 2) planes;
 // the time of a plane follows the 128-byte lines its loads and stores touch, per
-// population 3.8 ns in FP32 and FP64 and 4.3 ns in FP16, within 7% on periodic
+// population 3.8 ns in FP32 and FP64 and 4.3 ns in FP16, within 12% on periodic
 // lattices of 128^3 to 512^3 nodes, tiles 64 x 4 to 128 x 4, D3Q19 and D3Q27 (walled ones
-// 1.2 times that).  One step in place moves its populations at 5.5 TB/s, or at
-// 8.2 TB/s while the array stays in the 256 MB cache (up to about 230 MB).  Measured a
-// step, two in one pass against in place: 128^3 D3Q27 FP32 48 / 55 us, 96^3 21 / 25 us,
-// 64^3 8.9 / 8.5 us; FP16 128^3 39 / 31 us, 256^3 290 / 347 us.
+// 1.2 times that); long updates take longer: FP16 Smagorinsky and recursive 1.1 times (1.19
+// measured at 256 x 378 x 107, where two in one pass are 216 us a step against 211), walled
+// D3Q27 Smagorinsky in FP32, which spills, 1.22 (1.3 to 1.5 measured: 256 x 129 x 80 139
+// against 106, 256 x 256 x 200 414 against 563).  One step in place moves its populations at
+// 5.5 TB/s, or at 8.2 TB/s while the array stays in the 256 MB cache (up to about 230 MB).
+// Above that the rate falls: 269 MB 7.7 TB/s, 288 MB 6.8, 320 MB 6.1; with walls, whose
+// masks take their share, 256 MB 7.1, 270 MB 5.8; rows in 32-wide tiles 4.8 to 7.1 from
+// 235 MB on.  Measured a step, two in one pass against in place: 128^3 D3Q27 FP32 48 / 55 us, 96^3 21 / 25 us,
+// 64^3 8.9 / 8.5 us; FP16 128^3 39 / 31 us, 256^3 329 / 337 us.
 bool plan_two(lbm_lattice *L, bool tagged) {
     const lbm_config &c = L->cfg;
     const long long s = (long long)elem_bytes(c.prec), nxy = (long long)c.nx * c.ny;
@@ -254,9 +260,17 @@ bool plan_two(lbm_lattice *L, bool tagged) {
         }
     }
     if (best == 0.0) return false;
-    const double two_us = 4.0 + best * c.q * (c.prec == LBM_F16S ? 4.3e-3 : 3.8e-3) * (tagged ? 1.2 : 1.0);
-    const double bytes = (double)L->n_elems * s;
-    const double one_us = 3.0 + 2.0 * bytes / (bytes <= 230e6 ? 8.2e6 : 5.5e6);
+    const bool smag = (L->ms & MS_SMAG) != 0;
+    double longer = tagged ? 1.2 : 1.0;
+    if (c.prec == LBM_F16S && (smag || L->ms == MS_RR)) longer *= 1.1;
+    if (c.prec == LBM_F32 && c.q == 27 && tagged && smag) longer *= 1.22;
+    const double two_us = 4.0 + best * c.q * (c.prec == LBM_F16S ? 4.3e-3 : 3.8e-3) * longer;
+    const double bytes = (double)L->n_elems * s, over = bytes - 230e6;
+    double rate = 8.2e6;  // bytes a us
+    if (over > 0.0) {
+        rate = L->tx_log2 < 6 ? 5.5e6 : std::max(5.5e6, 8.2e6 - over * (tagged ? 2.7e6 / 60e6 : 2.7e6 / 100e6));
+    }
+    const double one_us = 3.0 + 2.0 * bytes / rate;
     return two_us < 0.95 * 2.0 * one_us;
 }
 

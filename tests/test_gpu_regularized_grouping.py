@@ -31,7 +31,7 @@ def _states(tags, q, prec, force, how):
 @pytest.mark.parametrize("q", [19, 27])
 @pytest.mark.parametrize("prec,geom", [("f64", "periodic"), ("f64", "walls"), ("f32", "periodic"), ("f32", "walls")])
 def test_grouping_and_launch_are_bitwise_irrelevant(prec, geom, q, tag, force):
-    nx, ny, nz = 192, 130, 141
+    nx, ny, nz = 210, 150, 141
     tags = inputs.all_fluid(nx, ny, nz, tag) if geom == "periodic" else \
         inputs.random_tags(nx, ny, nz, 11, 0.1, 0.05, (tag,))
     single = _states(tags, q, prec, force, "single")
@@ -40,7 +40,7 @@ def test_grouping_and_launch_are_bitwise_irrelevant(prec, geom, q, tag, force):
             assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("nx,ny,nz", [(256, 160, 160), (250, 254, 130)])
+@pytest.mark.parametrize("nx,ny,nz", [(256, 252, 124), (250, 254, 130)])
 @pytest.mark.parametrize("q,tag", [(19, lbm.TAG_REG), (27, lbm.TAG_REG), (27, lbm.TAG_RR)])
 def test_fp16_grouping_is_bitwise_irrelevant(nx, ny, nz, q, tag):
     tags = inputs.all_fluid(nx, ny, nz, tag)

@@ -35,7 +35,7 @@ def _check(tags, q, prec, force, torch_buffer=False):
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_periodic(prec, q, tag, force):
     """Rows that are not whole tiles, planes that are not whole blocks."""
-    _check(inputs.all_fluid(201, 130, 141, tag), q, prec, force)
+    _check(inputs.all_fluid(201, 150, 141, tag), q, prec, force)
 
 
 @pytest.mark.parametrize("force", FORCES)
@@ -44,17 +44,17 @@ def test_periodic(prec, q, tag, force):
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_walls(prec, q, tag, force):
     """Random solid and moving-wall nodes, also across the periodic edges."""
-    _check(inputs.random_tags(192, 130, 141, 11, 0.1, 0.05, (tag,)), q, prec, force)
+    _check(inputs.random_tags(210, 150, 141, 11, 0.1, 0.05, (tag,)), q, prec, force)
 
 
-@pytest.mark.parametrize("shape", [(256, 160, 160), (250, 254, 130)])
+@pytest.mark.parametrize("shape", [(256, 252, 124), (250, 254, 130)])
 @pytest.mark.parametrize("q,tag", [(19, lbm.TAG_BGK), (19, lbm.TAG_TRT), (19, lbm.TAG_REG)] + [(27, t) for t in MODELS])
 def test_fp16(shape, q, tag):
     _check(inputs.all_fluid(*shape, tag), q, "f16s", FORCES[0])
 
 
 def test_caller_buffer():
-    _check(inputs.all_fluid(201, 130, 141, lbm.TAG_BGK), 19, "f32", FORCES[0], torch_buffer=True)
+    _check(inputs.all_fluid(201, 150, 141, lbm.TAG_BGK), 19, "f32", FORCES[0], torch_buffer=True)
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16s"])
@@ -82,14 +82,32 @@ def test_full_size_taylor_green(prec):
 
 @pytest.mark.parametrize("tags,kw", [
     (lambda: inputs.all_fluid(64, 64, 64), dict(prec="f32")),                               # in the cache
-    (lambda: inputs.all_fluid(256, 160, 160), dict(prec="f16s", force=FORCES[1])),
-    (lambda: inputs.random_tags(256, 160, 160, 3, 0.02, 0.0), dict(prec="f16s")),           # walled FP16
+    (lambda: inputs.all_fluid(256, 252, 124), dict(prec="f16s", force=FORCES[1])),
+    (lambda: inputs.random_tags(256, 252, 124, 3, 0.02, 0.0), dict(prec="f16s")),           # walled FP16
     (lambda: inputs.random_tags(192, 130, 141, 3, 0.3, 0.0), dict(prec="f64")),             # over a quarter solid
     (lambda: inputs.all_fluid(192, 144, 144), dict(prec="f64", layout="bricks")),
     (lambda: inputs.all_fluid(192, 130, 141, lbm.TAG_MLP), dict(prec="f64")),
     (lambda: inputs.all_fluid(192, 130, 141), dict(prec="f64", free_stream=True))])
 def test_where_it_is_not_taken(tags, kw):
     with lbm.Lattice(tags(), q=19, **kw) as L:
+        assert L.steps_per_pass == 1
+
+
+def _cavity(nx, ny, nz, tag):
+    t = np.zeros((nz, ny, nx), dtype=np.uint8)
+    t[1:-1, 1:-1, 1:-1] = tag
+    t[nz - 1] = lbm.TAG_WALL0
+    return t
+
+
+@pytest.mark.parametrize("tags,kw", [
+    (lambda: _cavity(256, 79, 121, lbm.TAG_SMAG), dict(q=27, prec="f32")),      # 114 us a step, 91 in place
+    (lambda: _cavity(228, 50, 104, lbm.TAG_RR), dict(q=27, prec="f64")),        # 107, 75
+    (lambda: inputs.random_tags(256, 129, 80, 3, 0.15, 0.0, (lbm.TAG_SMAG,)), dict(q=27, prec="f32")),  # 139, 106
+    (lambda: inputs.all_fluid(285, 186, 47, lbm.TAG_TRT), dict(q=27, prec="f32"))])                     # 77, 73
+def test_where_it_would_be_slower(tags, kw):
+    """Lattices a little larger than the cache and long walled updates."""
+    with lbm.Lattice(tags(), **kw) as L:
         assert L.steps_per_pass == 1
 
 
