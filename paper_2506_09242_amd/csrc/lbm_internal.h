@@ -134,8 +134,9 @@ struct TwoTiles {
     int tx, ty, tiles_x, tiles_y, chunk;
     int n_blocks, per_xcd;    // blocks in all, and ceil(n_blocks / 8)
 };
-// Nodes of a tile with its halo, at most, by precision: 130 x 6 (two blocks' LDS
-// would not fit a CU in any case), in FP64 66 x 6 (LDS, and 256 registers a lane).
+// Nodes of a tile with its halo, at most, by precision: 130 x 6, in FP64 66 x 6 (LDS, and
+// 256 registers a lane).  One block fills a CU: in FP32 by its LDS, in FP16 (56 and 81 KB)
+// by its 13 waves, of which two blocks would put seven on a SIMD, 72 registers a lane.
 constexpr int two_region(int prec) { return prec == LBM_F64 ? 396 : 780; }
 constexpr int two_max_tx(int prec) { return prec == LBM_F64 ? 64 : 128; }
 // Lattices it is built for.  In FP16 two updates of a node cost more than the pass

@@ -535,8 +535,6 @@ __device__ __forceinline__ void collide_pairs(const C (&h)[Q], int tag, const St
     // rather than keep them from the momentum flux
     if constexpr (TWO && (TAGGED || !FORCE || Q == 27) && (MS & MS_SMAG) != 0) asm("" : "+v"(inv_rho), "+v"(uu15));
     hs[0] = fm(-fm(C(-V<Q, 0>::w), fm(C(-1.5) * rho, uu, drho), h[0]), wp, h[0]);
-    // rounded to FP32 before it is to FP16, as where the force's term follows
-    if constexpr (!FORCE) asm("" : "+v"(hs[0]));
     C gp = C(0), gm = C(0), uF3 = C(0);
     if constexpr (FORCE) {
         gp = fm(wp, C(-0.5), C(1));

@@ -447,8 +447,9 @@ struct TrainScratch {
     }
 };
 
-// Blocks of k_train: one per 128 samples up to 256, and at most 2048 samples a
-// wave beyond (the length of the FP32 sums over samples).
+// Blocks of k_train: one per 128 samples up to 256, beyond that one per 8192.  A gradient
+// entry is an FP32 sum over all samples of its block (one wave's accumulator), then
+// over the blocks in four runs.
 int train_blocks(long long n) {
     const long long b = (n + kTrainSamples - 1) / kTrainSamples;
     return (int)std::min(b, std::max(256ll, n / 8192));

@@ -19,8 +19,8 @@
 // Tile: the halo columns cost whole 128-byte lines in 2 (TY + 2) of the lines a
 // plane takes, so tiles are wide: measured on the 512^3 D3Q27 FP32 Taylor-Green
 // flow per step, one step per pass 5.21 ms; two per pass with 32 x 8 tiles (two
-// blocks a CU) 3.89, 64 x 8 3.44, 128 x 4 2.99 ms (1.27x the ideal reads from
-// the L2s at 64 x 8).  More blocks a CU are slower (their tiles no longer share
+// blocks a CU) 3.89, 64 x 8 3.44, 128 x 4 3.0 to 3.3 ms from box to box (1.27x the
+// ideal reads from the L2s at 64 x 8).  More blocks a CU are slower (their tiles no longer share
 // halos through a 4 MB L2): 3 a CU 4.96 ms.  Prefetching a plane earlier, or
 // two, gained nothing.
 #pragma once
@@ -176,6 +176,11 @@ __global__ __launch_bounds__(two_region(P) / 64 * 64 + 64) void k_two_steps(Step
             });
         }
     };
+    // a rest population is rounded to FP32 before it is to FP16, as in the one-step kernels
+    // of the models whose last product-sum is that of the force, also of a zero one
+    auto round_rest = [](C &h0) {
+        if constexpr (P == 2 && MS != MS_REG && MS != MS_RR) asm("" : "+v"(h0));
+    };
     // orders LDS accesses only: loads and stores of global memory stay in flight
     auto barrier = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -239,6 +244,7 @@ __global__ __launch_bounds__(two_region(P) / 64 * 64 + 64) void k_two_steps(Step
             if constexpr (TAGGED) wall_term(m_cur, ze, hs);
         }
         g[0] = rest;
+        round_rest(hs[0]);
         rest = (C)(S)hs[0];
         if constexpr (!RING3) {
             sfor<Q>([&](auto I) {
@@ -283,6 +289,7 @@ __global__ __launch_bounds__(two_region(P) / 64 * 64 + 64) void k_two_steps(Step
             C gs[Q];
             collide_node<Q, P, C, MS, TAGGED, FORCE, true>(g, tag_of(m_own), on, p, gs, P == 2 && PARITY == 1 && p.pair);
             if constexpr (TAGGED) wall_term(m_own, zo, gs);
+            round_rest(gs[0]);
             const unsigned own = lane_off(zo, yb[1], xb[1]);
             const int zv[3] = {wrapz(zo - 1), zo, wrapz(zo + 1)};
             const S *b[3] = {plane_base(dst, zv[0]), plane_base(dst, zv[1]), plane_base(dst, zv[2])};
